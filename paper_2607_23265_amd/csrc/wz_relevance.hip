@@ -344,8 +344,11 @@ constexpr uint32_t kBf16OneHi = 0x3F800000u;  // bf16 pair (0, 1)
 // store.
 constexpr int kTokWaves = 8;
 constexpr int kTokChunk = 64;      // channels per chunk (128 bytes of a bf16 row)
-constexpr int kTokRows = 64;       // tokens per tile at most (four 16-row MFMA tiles)
 constexpr int kTokPoolMax = 8192;  // channels whose sums are gathered in LDS
+constexpr size_t kTokLdsMax = 160 * 1024;  // LDS of a workgroup
+// Rows a wave stages for tiles of up to 8 * ipc tokens: whole 16-row MFMA
+// tiles (one to four).
+constexpr int tok_rows(int ipc) { return (ipc + 1) / 2 * 16; }
 constexpr int kTokQMax = 256;      // query tokens: at most four passes of 64 over a tile
 
 // POOL: the tile's channel sums are gathered in LDS (C <= kTokPoolMax) and
@@ -359,8 +362,15 @@ enum TokMode { kTokOne = 0, kTokGroups = 1, kTokPasses = 2 };
 // WV: the workgroup's waves.
 template <int NTG, int IPC, bool POOL, int MODE, int WV = kTokWaves>
 __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, const VideoArgs<StreamArgs> va) {
-  constexpr int kTokRowsPerThread = kTokRows * 8 / (WV * kWave);  // epilogue rows of a thread (8 threads a row)
-  static_assert(kTokRowsPerThread * WV * kWave == kTokRows * 8, "whole epilogue rows per thread");
+  // A tile's MFMAs, operand reads and staging cover the 16-row tiles it has
+  // tokens in, not the 64 rows a tile may hold, and the channel sums take the
+  // LDS of the C at hand: short clips, split into tiles of 13 to 32 tokens to
+  // fill the chip, did two to four times the contraction's work on rows of
+  // zeros, one workgroup to a CU.  Four videos of T = 16 (14x14, C = 3584, Q =
+  // 24) a call: 61.4 -> 47.5 us; T = 32, Q = 16: 25.5 -> 24.9 us.
+  constexpr int RT = tok_rows(IPC) / 16;
+  constexpr int kTokRows = 16 * RT;
+  constexpr int kTokRowsPerThread = (kTokRows * 8 + WV * kWave - 1) / (WV * kWave);  // epilogue rows of a thread (8 threads a row)
   const StreamArgs f = va.v[blockIdx.y];
   const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
   const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
@@ -369,11 +379,11 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
   // chunks of loads in flight per wave: two (eight waves keep 16 chunks of
   // the tile in flight; deeper rings measured slower)
   constexpr int D = 2;
-  // per-wave chunk buffers (16-byte units swizzled by row): rows 0 .. 63 of a
-  // wave's region stage its tile rows, rows 64 .. 64 + NQ - 1 its query rows;
-  // after the loop the region holds the wave's partial S [64 rows][NQ] floats
+  // per-wave chunk buffers (16-byte units swizzled by row): the first kTokRows
+  // rows of a wave's region stage its tile rows, the next NQ its query rows;
+  // after the loop the region holds the wave's partial S [kTokRows][NQ] floats
   __shared__ __align__(16) u32x4 s_xq[WV][kTokRows + NQ][8];
-  __shared__ __align__(16) float s_pool[POOL ? kTokPoolMax : 4];
+  extern __shared__ __align__(16) float s_pool[];  // [C] (POOL)
   __shared__ float s_xx[WV][kTokRows];
   __shared__ float s_qq[WV][NQ];
   __shared__ float s_rq[NQ];
@@ -420,9 +430,9 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
       for (int k = 0; k < QI; ++k) d.q[k] = buf_load_bf16x8(qres, ok ? (8 * k + lr) * C * 2 + cc * 2 : kOOB);
     };
 
-    f32x4 Sacc[4][NTG];
+    f32x4 Sacc[RT][NTG];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int n = 0; n < NTG; ++n) Sacc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
     float xx[IPC], qq[QI];
@@ -468,9 +478,9 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
     auto contract = [&]() {
 #pragma unroll
       for (int st = 0; st < 2; ++st) {
-        bf16x8 A[4], B[NTG];
+        bf16x8 A[RT], B[NTG];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < RT; ++i) {
           const int row = 16 * i + r16;
           A[i] = __builtin_bit_cast(bf16x8, s_xq[wave][row][(4 * st + grp) ^ (row & 7)]);
         }
@@ -482,12 +492,12 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
 #pragma unroll
         for (int n = 0; n < NTG; ++n)
 #pragma unroll
-          for (int i = 0; i < 4; ++i)
+          for (int i = 0; i < RT; ++i)
             Sacc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], B[n], Sacc[i][n], 0, 0, 0);
       }
     };
 
-    // rows this wave never loads (8 * IPC .. 63) are zero in its buffer
+    // rows this wave never loads (8 * IPC .. kTokRows - 1) are zero in its buffer
     for (int u = 8 * IPC * 8 + lane; u < kTokRows * 8; u += kWave) (&s_xq[wave][0][0])[u] = u32x4{0u, 0u, 0u, 0u};
 
     // A ring of D slots: the wave's chunks c, c + 8, ..., c + 8 (D - 1) are in
@@ -542,13 +552,13 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
       if (lu == 0) s_qq[wave][8 * k + lr] = v;
     }
     // sigma_j of the wave: its accumulator column j = 16 n + r16 summed over the
-    // wave's 64 rows (rows past the tile hold zeros), the four lane groups by
+    // wave's rows (rows past the tile hold zeros), the four lane groups by
     // lane swaps
 #pragma unroll
     for (int n = 0; n < NTG; ++n) {
       float v = 0.f;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int e = 0; e < 4; ++e) v += Sacc[i][n][e];
       const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -561,7 +571,7 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
     static_assert((kTokRows + NQ) * 8 * 16 >= kTokRows * NQ * 4, "partial S fits the wave's region");
     auto s_part = [&](int w, int r, int j) -> float& { return reinterpret_cast<float*>(&s_xq[w][0][0])[r * NQ + j]; };
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int n = 0; n < NTG; ++n)
 #pragma unroll
@@ -596,7 +606,8 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
     float sv[kTokRowsPerThread][CPT], x2[kTokRowsPerThread];
 #pragma unroll
     for (int k = 0; k < kTokRowsPerThread; ++k) {
-      const int row = (tid >> 3) + RS * k;
+      // (threads past the last row repeat it; their results are not written)
+      const int row = min((tid >> 3) + RS * k, kTokRows - 1);
 #pragma unroll
       for (int e = 0; e < CPT; ++e) {
         float v = 0.f;
@@ -616,11 +627,13 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
       // the rows' S_nj / |q_j| into LDS (wave 0's region: every read of the
       // partials is behind the last barrier); thread g of a row's eight takes
       // the maximum over query g's columns
-      float* s_cos = reinterpret_cast<float*>(&s_xq[0][0][0]);  // [64 rows][NQ]
+      float* s_cos = reinterpret_cast<float*>(&s_xq[0][0][0]);  // [kTokRows][NQ]
 #pragma unroll
       for (int k = 0; k < kTokRowsPerThread; ++k)
+        if ((tid >> 3) + RS * k < kTokRows) {
 #pragma unroll
-        for (int e = 0; e < CPT; ++e) s_cos[((tid >> 3) + RS * k) * NQ + cg + e] = sv[k][e] * rq[e];
+          for (int e = 0; e < CPT; ++e) s_cos[((tid >> 3) + RS * k) * NQ + cg + e] = sv[k][e] * rq[e];
+        }
       lds_barrier();
       const int g = tid & 7;
 #pragma unroll
@@ -1053,6 +1066,27 @@ void launch_mfma(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipS
                      pl.kc, va);
 }
 
+// LDS of a token-tiled workgroup without the gathered channel sums.
+constexpr size_t tok_lds(int ntg, int ipc, int wv) {
+  const int rows = tok_rows(ipc), nq = 16 * ntg;
+  return size_t(wv) * (rows + nq) * 128 + size_t(wv) * (rows + 2 * nq) * 4 + size_t(nq) * 4;
+}
+template <int NTG, int IPC, int MODE, int WV>
+void launch_tok_waves(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
+  // the channel sums are gathered in LDS up to 32 query columns (with 64,
+  // storing them chunk by chunk measured 1 % faster on full 64-token tiles:
+  // 160.0 against 161.4 us per call at T = 96, 27x27, C = 1152, Q = 48)
+  const size_t pool = size_t(va.v[0].C) * 4;
+  if constexpr (NTG <= 2) {
+    if (va.v[0].C <= kTokPoolMax && tok_lds(NTG, IPC, WV) + pool <= kTokLdsMax) {
+      hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, true, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), pool, s,
+                         pl.tile_tokens, va);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, false, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), 0, s,
+                     pl.tile_tokens, va);
+}
 template <int NTG, int IPC, int MODE>
 void launch_tok_mode(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
   const int C = va.v[0].C;
@@ -1061,32 +1095,13 @@ void launch_tok_mode(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, 
   // that size (64 query columns) takes four waves too: a wave's chunks set
   // the order in which each query's sums are added, so that each query's
   // results are bitwise those of its own pass.
-  const bool four = MODE == kTokGroups ? (va.v[0].qg + 15) / 16 == 2 && C <= kTokPoolMax
-                                       : NTG == 2 && MODE == kTokOne && C <= kTokPoolMax;
-  // with 64 query columns the staging regions leave no room for the gathered channel sums
-  if constexpr (NTG <= 2) {
-    if (C <= kTokPoolMax) {
-      if constexpr (NTG == 2 && MODE == kTokOne) {
-        if (four) {
-          hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, true, MODE, 4>), dim3(pl.grid, V), dim3(4 * kWave), 0, s,
-                             pl.tile_tokens, va);
-          return;
-        }
-      }
-      hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, true, MODE>), dim3(pl.grid, V), dim3(kTokWaves * kWave), 0, s,
-                         pl.tile_tokens, va);
+  if constexpr ((NTG == 2 && MODE == kTokOne) || (NTG == 4 && MODE == kTokGroups)) {
+    if (C <= kTokPoolMax && (MODE == kTokOne || (va.v[0].qg + 15) / 16 == 2)) {
+      launch_tok_waves<NTG, IPC, MODE, 4>(pl, va, V, s);
       return;
     }
   }
-  if constexpr (NTG == 4 && MODE == kTokGroups) {
-    if (four) {
-      hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, false, MODE, 4>), dim3(pl.grid, V), dim3(4 * kWave), 0, s,
-                         pl.tile_tokens, va);
-      return;
-    }
-  }
-  hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, false, MODE>), dim3(pl.grid, V), dim3(kTokWaves * kWave), 0, s,
-                     pl.tile_tokens, va);
+  launch_tok_waves<NTG, IPC, MODE, kTokWaves>(pl, va, V, s);
 }
 template <int NTG, int IPC>
 void launch_tok(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
