@@ -233,8 +233,8 @@ wz_status wz_condense_batch(const wz_config* cfg, int32_t videos, const void* X,
 /* Several queries over one video in one call: the whole pass of wz_condense
  * for each of `queries` queries of Q tokens (1 <= queries <= 8, else
  * WZ_ERR_SHAPE) on the same X, each with its own budgets and outputs.  The
- * paper scores every query afresh; here, when the inputs are bf16 and
- * Q <= 32, each pass over X serves a group of up to 64 / Q queries: their
+ * paper scores every query afresh; here, when Q <= 32, each pass over X
+ * serves a group of up to 64 / Q queries: their
  * tokens are the columns of one relevance contraction, and a_{t,n}, r_t and
  * the selection are taken per query.  Otherwise each query takes its own
  * pass over X (launched together, as in wz_condense_batch).  Layouts:

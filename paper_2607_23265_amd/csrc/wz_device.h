@@ -64,7 +64,7 @@ __device__ __forceinline__ void buf_store_wt_b64(uint64_t v, __amdgpu_buffer_rsr
 // rotation by 8), +-16 (permlane16 swap), +-32 (permlane32 swap); at each the
 // lane keeps the half its own index bit selects and adds the partner's copy
 // of it.  About 24 instructions instead of three reductions per value.
-__device__ __forceinline__ float lane_transpose_sum8(const float (&v)[8]) {
+__device__ __forceinline__ float lane_transpose_sum(const float (&v)[8]) {
   const int lane = __lane_id();
   const bool b0 = (lane >> 3) & 1;
   // step 1: keep the values of index parity b0 (m -> index 2m + b0)
@@ -86,6 +86,23 @@ __device__ __forceinline__ float lane_transpose_sum8(const float (&v)[8]) {
   // step 3: lower and upper 32 lanes (lane bit 5); the lower keep n = 0, the upper n = 1
   const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x[0]), __float_as_uint(x[1]), false, false);
   return __uint_as_float(s[0]) + __uint_as_float(s[1]);
+}
+
+// The same with four values a lane: lanes 8k + u and 8 (k + 4) + u, k < 4,
+// both end with value k's total.
+__device__ __forceinline__ float lane_transpose_sum(const float (&v)[4]) {
+  const bool b0 = (__lane_id() >> 3) & 1;
+  float w[2];
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const float keep = b0 ? v[2 * m + 1] : v[2 * m];
+    const float send = b0 ? v[2 * m] : v[2 * m + 1];
+    w[m] = keep + __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(send), 0x128, 0xF, 0xF, false));
+  }
+  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(w[0]), __float_as_uint(w[1]), false, false);
+  const float x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
 // Sum over the four 16-lane rows of a wave, every lane getting the total of

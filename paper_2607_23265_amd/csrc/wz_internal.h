@@ -44,7 +44,8 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 // tokens) and one slice of channels; tiles cover whole frames when H*W <= 256,
 // so the query, which every workgroup must read for its channels, is read
 // about once per frame, and channel slices give the grid enough workgroups.
-// Vector-ALU path: tiles of up to 32 tokens, all channels.
+// Vector-ALU path (small frames with many queries): tiles of up to 32 tokens,
+// all channels.
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;          // MI355X: workgroups are dealt to the 8 XCDs round robin
 constexpr int kCUs = 256;
@@ -57,14 +58,14 @@ constexpr int kTokMax = 4096;     // validated bound on tokens per frame
 inline int qpad(int Q) { return (Q + 3) & ~3; }
 
 // Streaming kernels of the relevance pass, chosen by shape:
-//   kRelTok  bf16, Q <= 64 or 128 < Q <= 256: token tiles with every
+//   kRelTok  fp32; bf16, Q <= 64 or 128 < Q <= 256: token tiles with every
 //            channel, each wave a channel stripe with its own LDS-transposed
 //            MFMA (above 64 query tokens, passes of 32 columns per tile);
 //   kRelWg   bf16, 64 < Q <= 128: token tiles with every channel, the
 //            workgroup's waves sharing each channel chunk of the tile and the
 //            query in LDS, each wave some 16-row tiles against every column;
 //   kRelMfma bf16, Q > 256, frames of >= 49 tokens: MFMA-layout loads;
-//   kRelValu everything else (fp32 inputs, small frames with many queries).
+//   kRelValu small bf16 frames with many queries.
 enum RelKind { kRelValu = 0, kRelMfma = 1, kRelTok = 2, kRelWg = 3 };
 RelKind relevance_kind(const wz_config& c);
 
@@ -96,8 +97,13 @@ inline RelPlan relevance_plan(const wz_config& c) {
     // query tiles: 1, 2 or 4 of 16 columns; above 64 columns, passes of 32
     const int nq = c.Q <= 16 ? 16 : c.Q <= 32 ? 32 : c.Q <= 64 ? 64 : 32;
     const int lo = (N + 63) / 64, hi = std::max(lo, (N + 15) / 16);
+    // fp32 inputs: tiles finer than 32 tokens (whose channel and column sums
+    // the workspace holds, T * tiles * (C + Q) floats) only while those stay
+    // under half of the allocation-free call's 32 MiB
+    const bool f32 = c.in_dtype != WZ_BF16;
     long best = -1;
     for (int k = lo; k <= hi; ++k) {
+      if (f32 && k > lo && k > (N + 31) / 32 && (long long)c.T * k * (c.C + c.Q) * 4 > (16LL << 20)) break;
       const int rows = (N + k - 1) / k + nq;
       const long cost = long((long(tr) * k + kCUs - 1) / kCUs) * rows;
       if (best < 0 || cost < best) best = cost, p.tiles = k;

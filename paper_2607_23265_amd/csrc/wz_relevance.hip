@@ -8,8 +8,8 @@
 // and forms r_t and delta_t (and a_{t,n} when a unit holds only some channels).
 //
 // Three decompositions, chosen by shape:
-//  * token tiles (bf16, Q <= 64; below): a workgroup owns up to 64 tokens of a
-//    frame with every channel, so a_{t,n} is final in the pass;
+//  * token tiles (fp32 inputs; bf16, Q <= 64; below): a workgroup owns up to
+//    64 tokens of a frame with every channel, so a_{t,n} is final in the pass;
 //  * MFMA layout (bf16, Q > 64, frames of >= 49 tokens): a workgroup owns one
 //    token tile of one frame (the whole frame when H*W <= 256; each wave holds
 //    two 16-row MFMA tiles) and one slice of at most 32 x 32 channels.  It
@@ -23,7 +23,7 @@
 //    and one wave per step adds the query's Gram matrix (diagonal: |q_j|^2).
 //    With one slice the workgroup also finishes its tokens' a_{t,n}; with
 //    several it writes the partial x . q_j and |x|^2;
-//  * vector ALU (fp32 inputs, small frames with many queries): tiles of up to
+//  * vector ALU (small frames with many queries): tiles of up to
 //    32 tokens over all channels, one wave per token, wave-reduced dot
 //    products.
 #include <type_traits>
@@ -317,10 +317,67 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
 // hardware reads as (0, 1) for a packed bf16 operand.
 constexpr uint32_t kBf16OneLo = 0x00003F80u;  // bf16 pair (1, 0)
 constexpr uint32_t kBf16OneHi = 0x3F800000u;  // bf16 pair (0, 1)
+// acc plus the square of a dword's channels (two bf16 or one fp32)
+template <typename In>
+__device__ __forceinline__ float norm_add(uint32_t v, float acc) {
+  if constexpr (sizeof(In) == 2) return dot2(v, v, acc);
+  else return fmaf(__uint_as_float(v), __uint_as_float(v), acc);
+}
+// The waves' partial sums get(0 .. WV - 1) in a fixed order: in turn, for fp32
+// inputs in pairs (fewer roundings of the large sums).
+template <typename In, int WV, typename Get>
+__device__ __forceinline__ float wave_add(Get get) {
+  float v[WV];
+#pragma unroll
+  for (int w = 0; w < WV; ++w) v[w] = get(w);
+  if constexpr (sizeof(In) == 2) {
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < WV; ++w) s += v[w];
+    return s;
+  } else {
+#pragma unroll
+    for (int d = 1; d < WV; d *= 2)
+#pragma unroll
+      for (int w = 0; w < WV; w += 2 * d) v[w] += v[w + d];
+    return v[0];
+  }
+}
+// acc[i][n] += the 16-row tiles A[i] times the 16-column tiles B[n] over the
+// 16-byte units that lane (row or column lane % 16, K group lane / 16) holds:
+// bf16, one MFMA over 32 channels; fp32, four over four channels each, MFMA e
+// taking element e of every lane's unit (the same channels of both operands),
+// so fp32 products are exact to fp32 rounding as on the vector ALU.
+template <typename In, int MT, int NT>
+__device__ __forceinline__ void mfma_units(const u32x4 (&A)[MT], const u32x4 (&B)[NT], f32x4 (&acc)[MT][NT]) {
+  if constexpr (sizeof(In) == 2) {
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+        acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[i]),
+                                                            __builtin_bit_cast(bf16x8, B[n]), acc[i][n], 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+          acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(A[i][e]), __uint_as_float(B[n][e]),
+                                                           acc[i][n], 0, 0, 0);
+  }
+}
 
 // ---------------------------------------------------------------------------
-// Token-tiled path (bf16, Q <= 64)
+// Token-tiled path (fp32 inputs; bf16, Q <= 64)
 // ---------------------------------------------------------------------------
+// (Described for bf16 inputs; an fp32 chunk is 32 channels, the same bytes,
+// and its S runs on v_mfma_f32_16x16x4_f32.  Bound for fp32: HBM up to about
+// 48 query tokens, above that the fp32 MFMA rate, a sixteenth of bf16's.  It
+// replaced one wave per token on the vector ALU, which read the whole query
+// from L2 for every token: T = 64, 14x14, C = 3584, Q = 32: 824 -> 51 us; T =
+// 8, 24x24, C = 2504, Q = 96: 1219 -> 56 us.)
 // A workgroup owns one tile of at most 64 tokens of one frame with ALL its
 // channels, so a_{t,n} is final here and no per-slice partial scores are
 // written; its tokens are one contiguous stretch of X.  The W waves (eight;
@@ -343,13 +400,13 @@ constexpr uint32_t kBf16OneHi = 0x3F800000u;  // bf16 pair (0, 1)
 // (|q_j| |x_n|) is formed, and the tile's channel sums leave in one coalesced
 // store.
 constexpr int kTokWaves = 8;
-constexpr int kTokChunk = 64;      // channels per chunk (128 bytes of a bf16 row)
+constexpr int kTokChunk = 64;      // channels per chunk (128 bytes of a bf16 row; 32 fp32 channels)
 constexpr int kTokPoolMax = 8192;  // channels whose sums are gathered in LDS
 constexpr size_t kTokLdsMax = 160 * 1024;  // LDS of a workgroup
 // Rows a wave stages for tiles of up to 8 * ipc tokens: whole 16-row MFMA
 // tiles (one to four).
 constexpr int tok_rows(int ipc) { return (ipc + 1) / 2 * 16; }
-constexpr int kTokQMax = 256;      // query tokens: at most four passes of 64 over a tile
+constexpr int kTokQMax = 256;      // bf16 query tokens: passes of 32 over a tile
 
 // POOL: the tile's channel sums are gathered in LDS (C <= kTokPoolMax) and
 // stored once at the end; otherwise a few lanes store them chunk by chunk.
@@ -360,7 +417,7 @@ constexpr int kTokQMax = 256;      // query tokens: at most four passes of 64 ov
 // a_{t,n} the maximum over the passes, the channel sums taken in the first.
 enum TokMode { kTokOne = 0, kTokGroups = 1, kTokPasses = 2 };
 // WV: the workgroup's waves.
-template <int NTG, int IPC, bool POOL, int MODE, int WV = kTokWaves>
+template <typename In, int NTG, int IPC, bool POOL, int MODE, int WV = kTokWaves>
 __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, const VideoArgs<StreamArgs> va) {
   // A tile's MFMAs, operand reads and staging cover the 16-row tiles it has
   // tokens in, not the 64 rows a tile may hold, and the channel sums take the
@@ -372,8 +429,12 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
   constexpr int kTokRows = 16 * RT;
   constexpr int kTokRowsPerThread = (kTokRows * 8 + WV * kWave - 1) / (WV * kWave);  // epilogue rows of a thread (8 threads a row)
   const StreamArgs f = va.v[blockIdx.y];
-  const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
-  const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
+  const In* __restrict__ X = static_cast<const In*>(f.X);
+  const In* __restrict__ query = static_cast<const In*>(f.query);
+  constexpr bool BF = sizeof(In) == 2;
+  constexpr int ES = int(sizeof(In));  // bytes of a channel
+  constexpr int CH = 128 / ES;         // channels per chunk
+  constexpr int CU = 16 / ES;          // channels per 16-byte unit
   constexpr int NQ = NTG * 16;  // query rows of the accumulators
   constexpr int QI = NQ / 8;    // query load instructions per chunk
   // chunks of loads in flight per wave: two (eight waves keep 16 chunks of
@@ -399,9 +460,9 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int r16 = lane & 15, grp = lane >> 4;  // MFMA layout: row / column, K group
   const int lr = lane >> 3, lu = lane & 7;     // load layout: row lr of each 8-row group, 16-byte unit lu
-  const int nch = (C + kTokChunk - 1) / kTokChunk;
+  const int nch = (C + CH - 1) / CH;
 
-  const __amdgpu_buffer_rsrc_t xres = make_rsrc_uniform(X + (size_t(t) * N + tok0) * C, uint32_t(TM) * C * 2);
+  const __amdgpu_buffer_rsrc_t xres = make_rsrc_uniform(X + (size_t(t) * N + tok0) * C, uint32_t(TM) * C * ES);
   constexpr bool GR = MODE == kTokGroups;
   const int npass = MODE == kTokPasses ? (Q + NQ - 1) / NQ : 1;
   float best_all[kTokRowsPerThread];
@@ -410,24 +471,24 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
   for (int h = 0; h < npass; ++h) {
     const int qb = h * NQ, Qh = min(NQ, Q - qb);
     const bool sums = h == 0;
-    const __amdgpu_buffer_rsrc_t qres = make_rsrc_uniform(query + size_t(qb) * C, uint32_t(Qh) * C * 2);
+    const __amdgpu_buffer_rsrc_t qres = make_rsrc_uniform(query + size_t(qb) * C, uint32_t(Qh) * C * ES);
 
     // ring slot: the tile's rows 8k + lr and the query's rows 8k + lr, unit lu
     // of the chunk; chunks past the end, rows past the tile or the query and
     // channels past C read zeros
     struct Slot {
-      bf16x8 x[IPC];
-      bf16x8 q[QI];
+      u32x4 x[IPC];
+      u32x4 q[QI];
     };
     // (query rows past Qh lie past the end of qres and read zeros; a per-lane
     // row test here would become a branch around the load)
     auto issue = [&](int c, Slot& d) {
-      const int cc = c * kTokChunk + 8 * lu;
+      const int cc = c * CH + CU * lu;
       const bool ok = c < nch && cc < C;
 #pragma unroll
-      for (int k = 0; k < IPC; ++k) d.x[k] = buf_load_bf16x8(xres, ok ? (8 * k + lr) * C * 2 + cc * 2 : kOOB);
+      for (int k = 0; k < IPC; ++k) d.x[k] = buf_load_u32x4(xres, ok ? (8 * k + lr) * C * ES + cc * ES : kOOB);
 #pragma unroll
-      for (int k = 0; k < QI; ++k) d.q[k] = buf_load_bf16x8(qres, ok ? (8 * k + lr) * C * 2 + cc * 2 : kOOB);
+      for (int k = 0; k < QI; ++k) d.q[k] = buf_load_u32x4(qres, ok ? (8 * k + lr) * C * ES + cc * ES : kOOB);
     };
 
     f32x4 Sacc[RT][NTG];
@@ -446,54 +507,79 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
 
     auto consume = [&](int c, const Slot& d) {
       // rows to LDS; |x|^2, |q_j|^2 and channel sums from the registers
-      float cs[8];
+      float cs[CU];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) cs[e] = 0.f;
+      for (int e = 0; e < CU; ++e) cs[e] = 0.f;
 #pragma unroll
       for (int k = 0; k < IPC; ++k) {
         const int row = 8 * k + lr;
-        const u32x4 v = __builtin_bit_cast(u32x4, d.x[k]);
+        const u32x4 v = d.x[k];
         s_xq[wave][row][lu ^ (row & 7)] = v;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          xx[k] = dot2(v[e], v[e], xx[k]);
-          cs[2 * e] = dot2(v[e], one_lo, cs[2 * e]);
-          cs[2 * e + 1] = dot2(v[e], one_hi, cs[2 * e + 1]);
+          xx[k] = norm_add<In>(v[e], xx[k]);
+          if constexpr (BF) {
+            cs[2 * e] = dot2(v[e], one_lo, cs[2 * e]);
+            cs[2 * e + 1] = dot2(v[e], one_hi, cs[2 * e + 1]);
+          } else {
+            cs[e] += __uint_as_float(v[e]);
+          }
         }
       }
 #pragma unroll
       for (int k = 0; k < QI; ++k) {
         const int row = 8 * k + lr;
-        const u32x4 v = __builtin_bit_cast(u32x4, d.q[k]);
+        const u32x4 v = d.q[k];
         s_xq[wave][kTokRows + row][lu ^ (row & 7)] = v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qq[k] = dot2(v[e], v[e], qq[k]);
+        for (int e = 0; e < 4; ++e) qq[k] = norm_add<In>(v[e], qq[k]);
       }
       // channel sums over the wave's rows (lanes lu, lu + 8, ..., lu + 56, in a
-      // fixed order): lane 8 lr + lu ends with channel 8 lu + lr's
-      const float cw = lane_transpose_sum8(cs);
-      const int c0 = c * kTokChunk + 8 * lu;
-      if (sums && c0 < C) pool[c0 + lr] = cw;
+      // fixed order): lane 8 lr + lu ends with unit lu's channel lr (fp32: lr % 4)
+      const float cw = lane_transpose_sum(cs);
+      const int c0 = c * CH + CU * lu;
+      if (sums && c0 < C && lr < CU) pool[c0 + lr] = cw;
     };
+    // 16-byte unit 4 st + grp of a staged row (16-row tiles start at multiples of 8 rows)
+    auto unit = [&](int row, int st) { return s_xq[wave][row][(4 * st + grp) ^ (row & 7)]; };
     auto contract = [&]() {
+      if constexpr (BF) {
 #pragma unroll
-      for (int st = 0; st < 2; ++st) {
-        bf16x8 A[RT], B[NTG];
+        for (int st = 0; st < 2; ++st) {
+          u32x4 A[RT], B[NTG];
 #pragma unroll
-        for (int i = 0; i < RT; ++i) {
-          const int row = 16 * i + r16;
-          A[i] = __builtin_bit_cast(bf16x8, s_xq[wave][row][(4 * st + grp) ^ (row & 7)]);
+          for (int i = 0; i < RT; ++i) A[i] = unit(16 * i + r16, st);
+#pragma unroll
+          for (int n = 0; n < NTG; ++n) B[n] = unit(kTokRows + 16 * n + r16, st);
+          mfma_units<In, RT, NTG>(A, B, Sacc);
         }
+      } else {
+        // fp32 inputs: half a chunk's products are summed from zero and added
+        // to the wave's sums once (chains of 16 products, then of the wave's
+        // half chunks): one chain of C / 8 products would round more often
+        // than the C / 64 of a lane-wise dot product.  At most two column
+        // tiles at a time, so that the partial sums fit the registers.
+        constexpr int NB = NTG < 2 ? NTG : 2;
 #pragma unroll
-        for (int n = 0; n < NTG; ++n) {
-          const int row = 16 * n + r16;
-          B[n] = __builtin_bit_cast(bf16x8, s_xq[wave][kTokRows + row][(4 * st + grp) ^ (row & 7)]);
-        }
+        for (int n0 = 0; n0 < NTG; n0 += NB)
 #pragma unroll
-        for (int n = 0; n < NTG; ++n)
+          for (int st = 0; st < 2; ++st) {
+            u32x4 A[RT], B[NB];
+            f32x4 part[RT][NB];
 #pragma unroll
-          for (int i = 0; i < RT; ++i)
-            Sacc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[i], B[n], Sacc[i][n], 0, 0, 0);
+            for (int i = 0; i < RT; ++i) A[i] = unit(16 * i + r16, st);
+#pragma unroll
+            for (int n = 0; n < NB; ++n) B[n] = unit(kTokRows + 16 * (n0 + n) + r16, st);
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+              for (int n = 0; n < NB; ++n) part[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+            mfma_units<In, RT, NB>(A, B, part);
+#pragma unroll
+            for (int i = 0; i < RT; ++i)
+#pragma unroll
+              for (int n = 0; n < NB; ++n) Sacc[i][n0 + n] += part[i][n];
+          }
       }
     };
 
@@ -558,9 +644,14 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
     for (int n = 0; n < NTG; ++n) {
       float v = 0.f;
 #pragma unroll
-      for (int i = 0; i < RT; ++i)
+      for (int i = 0; i < RT; ++i) {
+        if constexpr (BF) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v += Sacc[i][n][e];
+          for (int e = 0; e < 4; ++e) v += Sacc[i][n][e];
+        } else {
+          v += (Sacc[i][n][0] + Sacc[i][n][1]) + (Sacc[i][n][2] + Sacc[i][n][3]);
+        }
+      }
       const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
       v = __uint_as_float(a[0]) + __uint_as_float(a[1]);
       const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -578,12 +669,8 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
         for (int e = 0; e < 4; ++e) s_part(wave, 16 * i + 4 * grp + e, 16 * n + r16) = Sacc[i][n][e];
     lds_barrier();  // every sum below reads the waves' partials in wave order
     if (tid < Qh) {
-      float v = 0.f, qv = 0.f;
-#pragma unroll
-      for (int w = 0; w < WV; ++w) {
-        v += s_sig[w][tid];
-        qv += s_qq[w][tid];
-      }
+      const float v = wave_add<In, WV>([&](int w) { return s_sig[w][tid]; });
+      const float qv = wave_add<In, WV>([&](int w) { return s_qq[w][tid]; });
       if constexpr (GR) {
         const int g = tid / f.qg, j = tid - g * f.qg;
         advance(f.sig_part, g * f.gws)[(size_t(t) * f.tiles + tile) * f.qg + j] = v;
@@ -594,8 +681,7 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
       }
     }
     if (tid < NQ) {
-      float qv = 0.f;
-      for (int w = 0; w < WV; ++w) qv += s_qq[w][tid];
+      const float qv = wave_add<In, WV>([&](int w) { return s_qq[w][tid]; });
       s_rq[tid] = qv > 0.f ? 1.0f / sqrtf(qv) : 0.f;
     }
     // thread -> rows tid / 8 + RS k (k < kTokRowsPerThread), columns CPT * (tid % 8) .. + CPT - 1;
@@ -610,14 +696,9 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
       const int row = min((tid >> 3) + RS * k, kTokRows - 1);
 #pragma unroll
       for (int e = 0; e < CPT; ++e) {
-        float v = 0.f;
-#pragma unroll
-        for (int w = 0; w < WV; ++w) v += s_part(w, row, cg + e);
-        sv[k][e] = v;
+        sv[k][e] = wave_add<In, WV>([&](int w) { return s_part(w, row, cg + e); });
       }
-      x2[k] = 0.f;
-#pragma unroll
-      for (int w = 0; w < WV; ++w) x2[k] += s_xx[w][row];
+      x2[k] = wave_add<In, WV>([&](int w) { return s_xx[w][row]; });
     }
     lds_barrier();  // 1 / |q_j| in s_rq
     float rq[CPT];
@@ -791,7 +872,7 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
     }
     // the wave's channel sums (lanes lu, lu + 8, ..., lu + 56, in a fixed
     // order): lane 8 k + lu ends with channel 8 lu + k's
-    s_pp[b][wave][8 * lu + (lane >> 3)] = lane_transpose_sum8(cs);
+    s_pp[b][wave][8 * lu + (lane >> 3)] = lane_transpose_sum(cs);
   };
   // chunk c's channel sums, the waves' added in wave order by wave 0 (lane k:
   // channel k of the chunk).  Every lane of every wave issues the store (all
@@ -1071,7 +1152,7 @@ constexpr size_t tok_lds(int ntg, int ipc, int wv) {
   const int rows = tok_rows(ipc), nq = 16 * ntg;
   return size_t(wv) * (rows + nq) * 128 + size_t(wv) * (rows + 2 * nq) * 4 + size_t(nq) * 4;
 }
-template <int NTG, int IPC, int MODE, int WV>
+template <typename In, int NTG, int IPC, int MODE, int WV>
 void launch_tok_waves(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
   // the channel sums are gathered in LDS up to 32 query columns (with 64,
   // storing them chunk by chunk measured 1 % faster on full 64-token tiles:
@@ -1079,15 +1160,15 @@ void launch_tok_waves(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V,
   const size_t pool = size_t(va.v[0].C) * 4;
   if constexpr (NTG <= 2) {
     if (va.v[0].C <= kTokPoolMax && tok_lds(NTG, IPC, WV) + pool <= kTokLdsMax) {
-      hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, true, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), pool, s,
+      hipLaunchKernelGGL((k_relevance_tok<In, NTG, IPC, true, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), pool, s,
                          pl.tile_tokens, va);
       return;
     }
   }
-  hipLaunchKernelGGL((k_relevance_tok<NTG, IPC, false, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), 0, s,
+  hipLaunchKernelGGL((k_relevance_tok<In, NTG, IPC, false, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), 0, s,
                      pl.tile_tokens, va);
 }
-template <int NTG, int IPC, int MODE>
+template <typename In, int NTG, int IPC, int MODE>
 void launch_tok_mode(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
   const int C = va.v[0].C;
   // Four waves for a query of 17 to 32 tokens in one pass with the channel
@@ -1095,30 +1176,50 @@ void launch_tok_mode(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, 
   // that size (64 query columns) takes four waves too: a wave's chunks set
   // the order in which each query's sums are added, so that each query's
   // results are bitwise those of its own pass.
-  if constexpr ((NTG == 2 && MODE == kTokOne) || (NTG == 4 && MODE == kTokGroups)) {
+  if constexpr (sizeof(In) == 2 && ((NTG == 2 && MODE == kTokOne) || (NTG == 4 && MODE == kTokGroups))) {
     if (C <= kTokPoolMax && (MODE == kTokOne || (va.v[0].qg + 15) / 16 == 2)) {
-      launch_tok_waves<NTG, IPC, MODE, 4>(pl, va, V, s);
+      launch_tok_waves<In, NTG, IPC, MODE, 4>(pl, va, V, s);
       return;
     }
   }
-  launch_tok_waves<NTG, IPC, MODE, kTokWaves>(pl, va, V, s);
+  launch_tok_waves<In, NTG, IPC, MODE, kTokWaves>(pl, va, V, s);
 }
-template <int NTG, int IPC>
+template <typename In, int NTG, int IPC>
 void launch_tok(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
   if (va.v[0].groups > 1) {
-    launch_tok_mode<NTG, IPC, kTokGroups>(pl, va, V, s);
+    launch_tok_mode<In, NTG, IPC, kTokGroups>(pl, va, V, s);
   } else if (va.v[0].Q > 16 * NTG) {
     // the plan takes two query tiles for passes (checked by the caller)
-    if constexpr (NTG == 2) launch_tok_mode<NTG, IPC, kTokPasses>(pl, va, V, s);
+    if constexpr (NTG == 2) launch_tok_mode<In, NTG, IPC, kTokPasses>(pl, va, V, s);
   } else {
-    launch_tok_mode<NTG, IPC, kTokOne>(pl, va, V, s);
+    launch_tok_mode<In, NTG, IPC, kTokOne>(pl, va, V, s);
   }
+}
+
+template <typename In, int NTG>
+void launch_tok_tile(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
+  switch (pl.ipc) {
+    case 1: launch_tok<In, NTG, 1>(pl, va, V, s); break;
+    case 2: launch_tok<In, NTG, 2>(pl, va, V, s); break;
+    case 3: launch_tok<In, NTG, 3>(pl, va, V, s); break;
+    case 4: launch_tok<In, NTG, 4>(pl, va, V, s); break;
+    case 5: launch_tok<In, NTG, 5>(pl, va, V, s); break;
+    case 6: launch_tok<In, NTG, 6>(pl, va, V, s); break;
+    case 7: launch_tok<In, NTG, 7>(pl, va, V, s); break;
+    default: launch_tok<In, NTG, 8>(pl, va, V, s); break;
+  }
+}
+template <typename In>
+void launch_tok_shape(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
+  if (pl.ntg == 1) launch_tok_tile<In, 1>(pl, va, V, s);
+  else if (pl.ntg == 2) launch_tok_tile<In, 2>(pl, va, V, s);
+  else launch_tok_tile<In, 4>(pl, va, V, s);
 }
 
 }  // namespace
 
 RelKind relevance_kind(const wz_config& c) {
-  if (c.in_dtype != WZ_BF16) return kRelValu;
+  if (c.in_dtype != WZ_BF16) return kRelTok;  // passes of 32 columns above 64 query tokens
   if (c.Q > 64 && c.Q <= kWgQMax) return kRelWg;
   if (c.Q <= kTokQMax) return kRelTok;
   // two 16-row MFMA tiles per wave, at least 2 waves: frames of at least 49 tokens
@@ -1155,19 +1256,8 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
   if (pl.kind == kRelTok) {
     // columns beyond the query tiles are served by passes of two tiles only
     if (va.v[0].Q > 16 * pl.ntg && (pl.ntg != 2 || va.v[0].groups > 1)) return hipErrorInvalidValue;
-#define WZ_TOK(NTG)                                 \
-  switch (pl.ipc) {                                 \
-    case 1: launch_tok<NTG, 1>(pl, va, V, s); break; \
-    case 2: launch_tok<NTG, 2>(pl, va, V, s); break; \
-    case 3: launch_tok<NTG, 3>(pl, va, V, s); break; \
-    case 4: launch_tok<NTG, 4>(pl, va, V, s); break; \
-    case 5: launch_tok<NTG, 5>(pl, va, V, s); break; \
-    case 6: launch_tok<NTG, 6>(pl, va, V, s); break; \
-    case 7: launch_tok<NTG, 7>(pl, va, V, s); break; \
-    default: launch_tok<NTG, 8>(pl, va, V, s); break; \
-  }
-    if (pl.ntg == 1) { WZ_TOK(1) } else if (pl.ntg == 2) { WZ_TOK(2) } else { WZ_TOK(4) }
-#undef WZ_TOK
+    if (c.in_dtype == WZ_BF16) launch_tok_shape<uint16_t>(pl, va, V, s);
+    else launch_tok_shape<float>(pl, va, V, s);
   } else if (pl.kind == kRelWg) {
     if (va.v[0].groups > 1 || va.v[0].Q > kWgNQ) return hipErrorInvalidValue;
     if (pl.rtw == 1)
@@ -1178,10 +1268,8 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     // queries of more than 32 tokens take several passes of 32 over the slice:
     // wider query groups no longer fit the accumulators in registers
     launch_mfma<2>(pl, va, V, s);
-  } else if (c.in_dtype == WZ_BF16) {
-    hipLaunchKernelGGL((k_relevance_valu<uint16_t>), dim3(pl.grid, V), dim3(pl.threads), 0, s, pl.tile_tokens, va);
   } else {
-    hipLaunchKernelGGL((k_relevance_valu<float>), dim3(pl.grid, V), dim3(pl.threads), 0, s, pl.tile_tokens, va);
+    hipLaunchKernelGGL((k_relevance_valu<uint16_t>), dim3(pl.grid, V), dim3(pl.threads), 0, s, pl.tile_tokens, va);
   }
   return hipGetLastError();
 }
