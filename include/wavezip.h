@@ -151,12 +151,8 @@ wz_status wz_relevance(const wz_config* cfg, const void* X, const void* query,
 
 /* The pass over X that stage 1 starts with -- the one kernel of the whole
  * pass that reads the frames -- on its own.  It writes the per-token scores
- * a_{t,n} to tok_score [T*H*W] where one workgroup sees every channel of a
- * token (always for bf16 inputs with at most 256 query tokens and for fp32
- * inputs; for bf16 with more query tokens, when the grid has no channel
- * slices), and leaves in ws the per-work-unit partial sums that
- * wz_relevance's per-frame step completes r_t, delta_t (and, with channel
- * slices, a_{t,n}) from.  It
+ * a_{t,n} to tok_score [T*H*W] and leaves in ws the per-work-unit partial
+ * sums that wz_relevance's per-frame step completes r_t and delta_t from.  It
  * lets a caller run or time the pass alone; nothing else reads what it
  * leaves in ws.  Same arguments and checks as wz_relevance.  One kernel
  * launch.                                                                     */

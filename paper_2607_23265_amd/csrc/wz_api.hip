@@ -16,7 +16,6 @@ namespace {
 // address (on the host it is only a stand-in for the symbol): the device
 // address comes from hipGetSymbolAddress, once per device, with that device
 // current.
-constexpr size_t kScratchBytes = size_t(32) << 20;
 __device__ __align__(256) char scratch[kScratchBytes];
 
 constexpr int kMaxDevices = 64;

@@ -39,45 +39,35 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // ---------------------------------------------------------------------------
 // Decomposition of the relevance pass (shapes and limits; the kernels'
-// comments give the details).  Token-tiled path: tiles of at most 64 tokens
-// with every channel.  MFMA-layout path: a token tile of a frame (up to 256
-// tokens) and one slice of channels; tiles cover whole frames when H*W <= 256,
-// so the query, which every workgroup must read for its channels, is read
-// about once per frame, and channel slices give the grid enough workgroups.
-// Vector-ALU path (small frames with many queries): tiles of up to 32 tokens,
-// all channels.
+// comments give the details): token tiles of a frame, each with every channel.
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;          // MI355X: workgroups are dealt to the 8 XCDs round robin
 constexpr int kCUs = 256;
-constexpr int kMaxWaves = 16;     // 16-row MFMA tiles per token tile
-constexpr int kTilesPerWave = 2;  // 16-row MFMA tiles per wave on the MFMA path
-constexpr int kSliceSteps = 32;   // 32-channel steps per slice at most (the query slice sits in LDS)
 constexpr int kTokMax = 4096;     // validated bound on tokens per frame
 
-// Query columns of the per-slice partial scores, padded for 16-byte rows.
-inline int qpad(int Q) { return (Q + 3) & ~3; }
+// Scratch of the allocation-free call.
+constexpr size_t kScratchBytes = size_t(32) << 20;
 
 // Streaming kernels of the relevance pass, chosen by shape:
-//   kRelTok  fp32; bf16, Q <= 64 or 128 < Q <= 256: token tiles with every
-//            channel, each wave a channel stripe with its own LDS-transposed
-//            MFMA (above 64 query tokens, passes of 32 columns per tile);
-//   kRelWg   bf16, 64 < Q <= 128: token tiles with every channel, the
-//            workgroup's waves sharing each channel chunk of the tile and the
-//            query in LDS, each wave some 16-row tiles against every column;
-//   kRelMfma bf16, Q > 256, frames of >= 49 tokens: MFMA-layout loads;
-//   kRelValu small bf16 frames with many queries.
-enum RelKind { kRelValu = 0, kRelMfma = 1, kRelTok = 2, kRelWg = 3 };
+//   kRelTok  fp32; bf16, Q <= 64: token tiles, each wave a channel stripe with
+//            its own LDS-transposed MFMA (fp32 above 64 query tokens: passes
+//            of 32 columns per tile);
+//   kRelWg   bf16, 64 < Q <= 128: the workgroup's waves share each channel
+//            chunk of the tile and the query in LDS, each wave some 16-row
+//            tiles against every column;
+//   kRelWide bf16, Q > 128: the waves split the query's columns and share
+//            each chunk of the tile in LDS.
+enum RelKind { kRelTok = 0, kRelWg = 1, kRelWide = 2 };
 RelKind relevance_kind(const wz_config& c);
 
 struct RelPlan {
   RelKind kind;
   int tiles;        // token tiles per frame
   int tile_tokens;  // tokens per tile (the last tile of a frame may be shorter)
-  int mt;           // 16-row MFMA tiles per token tile (kRelMfma)
-  int slices;       // channel slices
-  int kc;           // channels per slice
-  int grid;         // workgroups: frames rounded up to a multiple of kXcds, x tiles x slices
-  int threads;      // threads per workgroup
+  int mt;           // kRelWide: 16-row MFMA tiles per stretch
+  int sub;          // kRelWide: stretches of a token tile
+  int ntw;          // kRelWide: 16-column tiles per wave
+  int grid;         // workgroups: frames rounded up to a multiple of kXcds, x tiles
   int ipc;          // kRelTok: row load instructions per chunk (tile rows / 8)
   int ntg;          // kRelTok, kRelWg: 16-column query tiles
   int rtw;          // kRelWg: 16-row tiles per wave (tiles of up to 64 * rtw tokens)
@@ -111,10 +101,6 @@ inline RelPlan relevance_plan(const wz_config& c) {
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.ipc = (p.tile_tokens + 7) / 8;
     p.ntg = nq / 16;
-    p.mt = 0;
-    p.slices = 1;
-    p.kc = c.C;
-    p.threads = 8 * 64;  // (the launcher takes four waves for one pass of two query tiles)
   } else if (p.kind == kRelWg) {
     // tiles of at most 128 tokens; two workgroups share a CU.  Every
     // workgroup streams its tile's rows and the whole query through LDS:
@@ -131,49 +117,42 @@ inline RelPlan relevance_plan(const wz_config& c) {
     }
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.rtw = p.tile_tokens <= 64 ? 1 : 2;
-    p.mt = 0;
-    p.slices = 1;
-    p.kc = c.C;
-    p.threads = 256;
-  } else if (p.kind == kRelMfma) {
-    const int cap = 16 * kMaxWaves;
-    p.tiles = (N + cap - 1) / cap;
-    p.tile_tokens = (N + p.tiles - 1) / p.tiles;
-    p.mt = (p.tile_tokens + 15) / 16;
-    const int ksteps = (c.C + 31) / 32;
-    // slices of at most kSliceSteps steps; more while the grid is short of
-    // one workgroup per CU, keeping slices of at least 8 channel steps and
-    // per-slice partial scores (4*Q bytes a token) under a quarter of X (2*C)
-    const int smin = (ksteps + kSliceSteps - 1) / kSliceSteps;
-    const int smax = std::max(smin, std::min(ksteps / 8, c.C / (8 * c.Q)));
-    int S = smin;
-    while (S < smax && (long long)c.T * p.tiles * S < kCUs) ++S;
-    const int kper = (ksteps + S - 1) / S;
-    p.kc = kper * 32;
-    p.slices = (ksteps + kper - 1) / kper;
-    p.threads = (p.mt + kTilesPerWave - 1) / kTilesPerWave * 64;
   } else {
-    const int cap = 32;
-    p.tiles = (N + cap - 1) / cap;
+    // passes of up to 384 columns; tiles of 16 to 64 tokens, one workgroup to a
+    // CU.  Per 64 channels a workgroup's MFMAs take as long as 16-row tiles x
+    // column tiles, its query reads from L2 as long as four 16-row tiles do:
+    // take the tile count with the least of their sum over a CU's turns, the
+    // smaller count on a tie
+    const int passes = (c.Q + 383) / 384;
+    p.ntw = (c.Q + 128 * passes - 1) / (128 * passes);
+    const int tr = (c.T + kXcds - 1) / kXcds * kXcds;
+    const int lo = (N + 63) / 64, hi = (N + 15) / 16;
+    long best = -1;
+    for (int k = lo; k <= hi; ++k) {
+      const int rows = ((N + k - 1) / k + 15) / 16 * 16;
+      const long cost = long((long(tr) * k + kCUs - 1) / kCUs) * (rows + 64);
+      if (best < 0 || cost < best) best = cost, p.tiles = k;
+    }
+    // The tiles' channel and column sums are the workspace's largest part: where
+    // they would take the call past the allocation-free scratch (with 20 bytes
+    // a token for scores, ranks and gates, and the alignment of the arrays),
+    // tiles of up to 256 tokens, in stretches of at most 64
+    const size_t rest = size_t(c.T) * (c.Q * 4 + size_t(N) * 20 + 16) + 16 * 256;
+    if (size_t(c.T) * p.tiles * (size_t(c.C) + c.Q) * 4 + rest > kScratchBytes) p.tiles = (N + 255) / 256;
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
-    p.mt = (p.tile_tokens + 15) / 16;
-    p.slices = 1;
-    p.kc = c.C;
-    p.threads = 256;
+    p.sub = (p.tile_tokens + 63) / 64;
+    p.mt = ((p.tile_tokens + p.sub - 1) / p.sub + 15) / 16;
   }
-  p.grid = (c.T + kXcds - 1) / kXcds * kXcds * p.tiles * p.slices;
+  p.grid = (c.T + kXcds - 1) / kXcds * kXcds * p.tiles;
   return p;
 }
 
-// Workgroup b works on frame t = (b / kXcds / (tiles*slices)) * kXcds + b % kXcds,
+// Workgroup b works on frame t = (b / kXcds / tiles) * kXcds + b % kXcds,
 // so every workgroup of a frame runs on the same XCD.
-__device__ __forceinline__ void unit_of_block(int b, int tiles, int slices, int& t, int& tile, int& slice) {
+__device__ __forceinline__ void unit_of_block(int b, int tiles, int& t, int& tile) {
   const int xcd = b % kXcds, slot = b / kXcds;
-  const int per_frame = tiles * slices;
-  const int r = slot % per_frame;
-  t = (slot / per_frame) * kXcds + xcd;
-  tile = r / slices;
-  slice = r % slices;
+  t = (slot / tiles) * kXcds + xcd;
+  tile = slot % tiles;
 }
 
 constexpr int kMaxFrames = 2048;
@@ -188,10 +167,8 @@ constexpr int kFusedTMax = 256;
 size_t filter_rows_bytes(const wz_config& c);
 
 struct Workspace {
-  float* s_part;       // [T][slices][N][qpad(Q)] per-slice x . q_j (only with several slices)
-  float* g_part;       // [T][slices][N]          per-slice |x|^2 (only with several slices)
-  float* qg_part;      // [T][slices][Q]          per-slice |q_j|^2
-  float* sig_part;     // [T][tiles][slices][Q]   per-unit sums over tokens of x . q_j
+  float* qg_part;      // [T][Q]                  |q_j|^2
+  float* sig_part;     // [T][tiles][Q]           per-tile sums over tokens of x . q_j
   float* pool_part;    // [T][tiles][C]           per-tile channel sums
   float* tok_score;    // [T*N]
   int32_t* rank;       // [T*N]                   selection rank of each token in its frame
@@ -212,15 +189,12 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 // (without it the modulator runs its fused form, which keeps them in LDS).
 inline Workspace workspace_layout(const wz_config& c, char* base, bool split = true) {
   const RelPlan pl = relevance_plan(c);
-  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q, QP = qpad(c.Q), tiles = pl.tiles,
-               S = pl.slices;
+  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q, tiles = pl.tiles;
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + off : nullptr; off += align256(bytes); return p; };
-  w.s_part = reinterpret_cast<float*>(take(S > 1 ? T * S * N * QP * 4 : 0));
-  w.g_part = reinterpret_cast<float*>(take(S > 1 ? T * S * N * 4 : 0));
-  w.qg_part = reinterpret_cast<float*>(take(T * S * Q * 4));
-  w.sig_part = reinterpret_cast<float*>(take(T * tiles * S * Q * 4));
+  w.qg_part = reinterpret_cast<float*>(take(T * Q * 4));
+  w.sig_part = reinterpret_cast<float*>(take(T * tiles * Q * 4));
   w.pool_part = reinterpret_cast<float*>(take(T * tiles * C * 4));
   w.tok_score = reinterpret_cast<float*>(take(T * N * 4));
   w.rank = reinterpret_cast<int32_t*>(take(T * N * 4));
@@ -265,8 +239,6 @@ __host__ __device__ inline P* advance(P* p, long long bytes) {
 }
 inline Workspace advance(const Workspace& w, long long bytes) {
   Workspace o = w;
-  o.s_part = advance(w.s_part, bytes);
-  o.g_part = advance(w.g_part, bytes);
   o.qg_part = advance(w.qg_part, bytes);
   o.sig_part = advance(w.sig_part, bytes);
   o.pool_part = advance(w.pool_part, bytes);
@@ -285,11 +257,10 @@ inline Workspace advance(const Workspace& w, long long bytes) {
 
 // Kernel launchers (each returns hipGetLastError() of its launches; `vs`
 // batches videos, one by default).
-// Streaming pass of stage 1: per-unit partials into ws (and a_{t,n} into
-// tok_score when there is one channel slice).
+// Streaming pass of stage 1: per-tile partials into ws, a_{t,n} into tok_score.
 hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void* query, float* tok_score,
                                    const Workspace& ws, hipStream_t s, const Videos& vs = Videos{});
-// Per-frame finish of stage 1: a_{t,n} (several slices), r_t and delta_t;
+// Per-frame finish of stage 1: r_t and delta_t;
 // with `order` also every frame's selection ranks and block gates (into
 // ws.rank, ws.byrank, ws.gate) for launch_assign_gather.
 hipError_t launch_frame(const wz_config& c, const Workspace& ws, float* tok_score, float* frame_rel,

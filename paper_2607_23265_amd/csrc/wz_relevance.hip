@@ -4,28 +4,16 @@
 //     x . q_j  (all j),  |x|^2,  |q_j|^2,
 // and per frame the channel sums p_t = sum_n x_{t,n} (the mean's cosine is the
 // sum's) and sigma_j = sum_n x_{t,n} . q_j = p_t . q_j.  It writes them per
-// work unit; the per-frame kernel adds the units' partials in a fixed order
-// and forms r_t and delta_t (and a_{t,n} when a unit holds only some channels).
+// work unit (and a_{t,n}, final); the per-frame kernel adds the units' partials
+// in a fixed order and forms r_t and delta_t.
 //
-// Three decompositions, chosen by shape:
-//  * token tiles (fp32 inputs; bf16, Q <= 64; below): a workgroup owns up to
-//    64 tokens of a frame with every channel, so a_{t,n} is final in the pass;
-//  * MFMA layout (bf16, Q > 64, frames of >= 49 tokens): a workgroup owns one
-//    token tile of one frame (the whole frame when H*W <= 256; each wave holds
-//    two 16-row MFMA tiles) and one slice of at most 32 x 32 channels.  It
-//    stages the slice of the query (MFMA B layout) in LDS, where every wave
-//    reads it; X streams into A-operand registers through an R-deep ring of
-//    16-byte buffer loads with no barrier in the loop.  Per 32-channel step
-//    each wave runs v_mfma_f32_16x16x32_bf16 for
-//        S += X Q^T      (the relevance contraction),
-//        G += X X^T      (diagonal: |x|^2),
-//        P += X I        (identity columns: channel sums of its tokens),
-//    and one wave per step adds the query's Gram matrix (diagonal: |q_j|^2).
-//    With one slice the workgroup also finishes its tokens' a_{t,n}; with
-//    several it writes the partial x . q_j and |x|^2;
-//  * vector ALU (small frames with many queries): tiles of up to
-//    32 tokens over all channels, one wave per token, wave-reduced dot
-//    products.
+// Three decompositions, each with every channel in a workgroup:
+//  * token tiles (fp32 inputs; bf16, Q <= 64): a workgroup owns up to 64 tokens
+//    of a frame, its waves split the channels;
+//  * shared token tiles (bf16, 64 < Q <= 128): the waves share each chunk of
+//    the tile and of the query in LDS and split S;
+//  * wide queries (bf16, Q > 128): the waves split the query's columns, which
+//    they read from L2, and share the tile in LDS.
 #include <type_traits>
 
 #include "wz_device.h"
@@ -33,20 +21,15 @@
 namespace wz {
 namespace {
 
-constexpr int kKStep = 32;    // channels per MFMA K step (16x16x32)
-constexpr int kQMax = 1024;   // validated bound on query tokens
-
 // Per-unit outputs of the streaming pass (layouts in the workspace carve-up).
 struct StreamArgs {
   const void* X;      // [T][H][W][C]
   const void* query;  // [Q][C]
-  float* s_part;
-  float* g_part;
   float* qg_part;
   float* sig_part;
   float* pool_part;
-  float* tok_score;  // written here when there is one slice
-  int T, N, C, Q, QP, tiles, slices;
+  float* tok_score;
+  int T, N, C, Q, tiles;
   // several queries in one pass (token-tiled path): `query` holds groups x qg
   // rows (Q = groups * qg); query g's scores, column sums and norms go to the
   // buffers above advanced by g * gws bytes, its channel sums are query 0's
@@ -54,257 +37,6 @@ struct StreamArgs {
   long long gws = 0;
 };
 static_assert(sizeof(VideoArgs<StreamArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
-
-// ---------------------------------------------------------------------------
-// MFMA path
-// ---------------------------------------------------------------------------
-// NTG: 16-column query tiles per pass over the slice (queries of more tokens
-// take several passes); R: depth of the X prefetch ring in 32-channel steps.
-template <int NTG, int R>
-__global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_mfma(
-    int tile_tokens, int kc, const VideoArgs<StreamArgs> va) {
-  const StreamArgs f = va.v[blockIdx.y];
-  const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
-  const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
-  constexpr int MTW = kTilesPerWave;
-  constexpr int MAXW = kMaxWaves / MTW;
-  constexpr int QB = 8;                          // query units staged per thread per batch
-  __shared__ u32x4 s_q[kSliceSteps][NTG][kWave];  // the group's query slice, MFMA B layout
-  __shared__ float s_poolw[MAXW][kSliceSteps * kKStep];  // per-wave channel sums of the slice
-  __shared__ float s_colw[MAXW][NTG * 16];       // per-wave column sums of S
-  __shared__ float s_qgw[MAXW][NTG * 16];        // per-wave |q_j|^2 partials
-  __shared__ float s_xt[kMaxWaves * 16];         // |x| of the tile's tokens (one slice)
-  __shared__ float s_rq[kQMax];                 // 1/|q_j| (one slice)
-
-  int t, tile, sl;
-  unit_of_block(blockIdx.x, f.tiles, f.slices, t, tile, sl);
-  if (t >= f.T) return;
-  const int N = f.N, C = f.C, Q = f.Q, QP = f.QP, S = f.slices;
-  const int tok0 = tile * tile_tokens;
-  const int TM = min(tile_tokens, N - tok0);
-  const int tid = threadIdx.x, nthreads = blockDim.x;
-  // wave index in a scalar register: branches on it must be scalar branches,
-  // since an MFMA under an exec mask still updates every lane
-  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nthreads >> 6;
-  const int row = lane & 15, grp = lane >> 4;
-  const int c_lo = sl * kc, c_hi = min(C, c_lo + kc);
-  const int kper = (c_hi - c_lo + kKStep - 1) / kKStep;  // <= kSliceSteps
-
-  const __amdgpu_buffer_rsrc_t xres = make_rsrc(X + (size_t(t) * N + tok0) * C, uint32_t(TM) * C * 2);
-  const __amdgpu_buffer_rsrc_t qres = make_rsrc(query, uint32_t(Q) * C * 2);
-  int xoff[MTW];  // byte offsets of this lane's token rows (A operands) in the tile
-#pragma unroll
-  for (int i = 0; i < MTW; ++i) {
-    const int r = (wave * MTW + i) * 16 + row;
-    xoff[i] = r < TM ? r * C * 2 : kOOB;
-  }
-
-  // identity operands: slot e of the lane with column `row`, K group `grp`
-  // holds channel 8*grp + e of the step; I_s selects channel 16*s + column
-  bf16x8 I0, I1;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    I0[e] = (__bf16)((8 * grp + e == row) ? 1.0f : 0.0f);
-    I1[e] = (__bf16)((8 * grp + e == 16 + row) ? 1.0f : 0.0f);
-  }
-
-  f32x4 G[MTW];
-  float best[MTW][4];  // rows 16*(wave*MTW+i) + 4*grp + e (one slice only)
-#pragma unroll
-  for (int i = 0; i < MTW; ++i) {
-    G[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) best[i][e] = -INFINITY;
-  }
-  const int groups = (Q + NTG * 16 - 1) / (NTG * 16);
-
-  bf16x8 a[R][MTW];  // X prefetch ring: slot r holds the steps ks = r (mod R)
-  auto issue = [&](int ks, bf16x8 (&dst)[MTW]) {
-    const int c = c_lo + ks * kKStep + grp * 8;
-    const bool ok = ks < kper && c < c_hi;
-#pragma unroll
-    for (int i = 0; i < MTW; ++i) dst[i] = buf_load_bf16x8(xres, ok ? xoff[i] + c * 2 : kOOB);
-  };
-
-  for (int g = 0; g < groups; ++g) {
-    const int qg0 = g * NTG * 16;
-    f32x4 Sacc[MTW][NTG], QG[NTG];
-#pragma unroll
-    for (int n = 0; n < NTG; ++n) {
-      QG[n] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int i = 0; i < MTW; ++i) Sacc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-
-    // X ring first, then the query slice of the group into LDS: unit
-    // u -> step u / (64 NTG), tile (u / 64) % NTG, lane u % 64
-#pragma unroll
-    for (int r = 0; r < R; ++r) issue(r, a[r]);
-    const int qunits = kper * NTG * kWave;
-    for (int u0 = 0; u0 < qunits; u0 += QB * nthreads) {
-      u32x4 qv[QB];
-#pragma unroll
-      for (int k = 0; k < QB; ++k) {
-        const int u = u0 + tid + k * nthreads;
-        const int l = u & 63, n = (u >> 6) % NTG, ks = u / (NTG * kWave);
-        const int j = qg0 + n * 16 + (l & 15);
-        const int c = c_lo + ks * kKStep + (l >> 4) * 8;
-        const bool ok = u < qunits && j < Q && c < c_hi;
-        qv[k] = buf_load_u32x4(qres, ok ? (j * C + c) * 2 : kOOB);
-      }
-#pragma unroll
-      for (int k = 0; k < QB; ++k) {
-        const int u = u0 + tid + k * nthreads;
-        if (u < qunits) s_q[u / (NTG * kWave)][(u >> 6) % NTG][u & 63] = qv[k];
-      }
-    }
-    __syncthreads();
-
-    auto compute = [&](int ks, const bf16x8 (&x)[MTW], auto pool) {
-      bf16x8 b[NTG];
-#pragma unroll
-      for (int n = 0; n < NTG; ++n) b[n] = __builtin_bit_cast(bf16x8, s_q[ks][n][lane]);
-#pragma unroll
-      for (int n = 0; n < NTG; ++n)
-#pragma unroll
-        for (int i = 0; i < MTW; ++i)
-          Sacc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], b[n], Sacc[i][n], 0, 0, 0);
-      if (ks % nw == wave) {
-        // query Gram matrix of the step (diagonal: |q_j|^2), spread over the waves
-#pragma unroll
-        for (int n = 0; n < NTG; ++n) QG[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[n], b[n], QG[n], 0, 0, 0);
-      }
-      if constexpr (decltype(pool)::value) {
-        f32x4 P0 = {0.f, 0.f, 0.f, 0.f}, P1 = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < MTW; ++i) {
-          G[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], x[i], G[i], 0, 0, 0);
-          P0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], I0, P0, 0, 0, 0);
-          P1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], I1, P1, 0, 0, 0);
-        }
-        float v0 = (P0[0] + P0[1]) + (P0[2] + P0[3]);
-        float v1 = (P1[0] + P1[1]) + (P1[2] + P1[3]);
-        v0 = row_sum4(v0);
-        v1 = row_sum4(v1);
-        // lanes 0-15: channels 32ks+0..15 of the slice, lanes 16-31: 32ks+16..31
-        if (lane < 32) s_poolw[wave][ks * kKStep + lane] = lane < 16 ? v0 : v1;
-      }
-    };
-    // Steps 2s and 2s+1 read the two 64-byte halves of the same 128-byte
-    // line of each row, so they are consumed and re-issued as a pair: the
-    // second request of a line then finds the first one's miss in flight
-    // instead of a line the cache may have evicted meanwhile.
-    static_assert(R % 2 == 0, "the ring advances in pairs of steps");
-    auto run = [&](auto pool) {
-      for (int ks0 = 0; ks0 < kper; ks0 += R) {
-#pragma unroll
-        for (int r = 0; r < R; r += 2) {
-          const int ks = ks0 + r;
-          if (ks < kper) compute(ks, a[r], pool);
-          if (ks + 1 < kper) compute(ks + 1, a[r + 1], pool);
-          issue(ks + R, a[r]);
-          issue(ks + 1 + R, a[r + 1]);
-        }
-      }
-    };
-    if (g == 0) run(std::true_type{});
-    else run(std::false_type{});
-    __syncthreads();
-
-    // ---- group epilogue ----
-    const bool diag = (row >> 2) == grp;  // lane holds element (row, row) of a 16x16 tile
-    if (diag) {
-#pragma unroll
-      for (int n = 0; n < NTG; ++n) s_qgw[wave][n * 16 + row] = QG[n][row & 3];
-    }
-#pragma unroll
-    for (int n = 0; n < NTG; ++n) {
-      float v = 0.f;
-#pragma unroll
-      for (int i = 0; i < MTW; ++i) v += (Sacc[i][n][0] + Sacc[i][n][1]) + (Sacc[i][n][2] + Sacc[i][n][3]);
-      v = row_sum4(v);
-      if (lane < 16) s_colw[wave][n * 16 + lane] = v;
-    }
-    if (g == 0) {
-      const __amdgpu_buffer_rsrc_t gres = make_rsrc(f.g_part + (size_t(t) * S + sl) * N, S > 1 ? uint32_t(N) * 4 : 0u);
-      if (diag) {
-#pragma unroll
-        for (int i = 0; i < MTW; ++i) {
-          const int r = (wave * MTW + i) * 16 + row;
-          const float gg = G[i][row & 3];
-          if (S == 1) s_xt[r] = sqrtf(gg);
-          else buf_store_f32(gg, gres, r < TM ? (tok0 + r) * 4 : kOOB);
-        }
-      }
-      // the slice's channel sums, waves added in order
-      const __amdgpu_buffer_rsrc_t pres =
-          make_rsrc(f.pool_part + (size_t(t) * f.tiles + tile) * C, uint32_t(C) * 4);
-      for (int c = tid; c < kper * kKStep; c += nthreads) {
-        float s = 0.f;
-        for (int w = 0; w < nw; ++w) s += s_poolw[w][c];
-        buf_store_f32(s, pres, c_lo + c < c_hi ? (c_lo + c) * 4 : kOOB);
-      }
-    }
-    __syncthreads();
-    if (tid < NTG * 16) {
-      const int j = qg0 + tid;
-      float qq = 0.f, sg = 0.f;
-      for (int w = 0; w < nw; ++w) {
-        qq += s_qgw[w][tid];
-        sg += s_colw[w][tid];
-      }
-      if (j < Q) {
-        if (S == 1) s_rq[j] = qq > 0.f ? 1.0f / sqrtf(qq) : 0.f;
-        if (tile == 0) f.qg_part[(size_t(t) * S + sl) * Q + j] = qq;
-        f.sig_part[((size_t(t) * f.tiles + tile) * S + sl) * Q + j] = sg;
-      }
-    }
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t sres =
-        make_rsrc(f.s_part + (size_t(t) * S + sl) * N * QP, S > 1 ? uint32_t(N) * QP * 4 : 0u);
-#pragma unroll
-    for (int n = 0; n < NTG; ++n) {
-      const int j = qg0 + n * 16 + row;  // this lane's column
-      if (S == 1) {
-        const float rq = j < Q ? s_rq[j] : 0.f;
-#pragma unroll
-        for (int i = 0; i < MTW; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) best[i][e] = fmaxf(best[i][e], j < Q ? Sacc[i][n][e] * rq : -INFINITY);
-      } else {
-#pragma unroll
-        for (int i = 0; i < MTW; ++i)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int r = (wave * MTW + i) * 16 + 4 * grp + e;
-            buf_store_f32(Sacc[i][n][e], sres, (r < TM && j < Q) ? ((tok0 + r) * QP + j) * 4 : kOOB);
-          }
-      }
-    }
-  }
-
-  if (S == 1) {
-    // max over the 16 columns held by the lanes of this K group
-#pragma unroll
-    for (int i = 0; i < MTW; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) best[i][e] = fmaxf(best[i][e], __shfl_xor(best[i][e], m, kWave));
-    if (row == 0) {
-#pragma unroll
-      for (int i = 0; i < MTW; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = (wave * MTW + i) * 16 + 4 * grp + e;
-          if (r < TM) {
-            const float xn = s_xt[r];
-            f.tok_score[size_t(t) * N + tok0 + r] = xn > 0.f ? best[i][e] / xn : 0.f;
-          }
-        }
-    }
-  }
-}
 
 // bf16 dot2 helpers of the token-tiled path
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -406,7 +138,6 @@ constexpr size_t kTokLdsMax = 160 * 1024;  // LDS of a workgroup
 // Rows a wave stages for tiles of up to 8 * ipc tokens: whole 16-row MFMA
 // tiles (one to four).
 constexpr int tok_rows(int ipc) { return (ipc + 1) / 2 * 16; }
-constexpr int kTokQMax = 256;      // bf16 query tokens: passes of 32 over a tile
 
 // POOL: the tile's channel sums are gathered in LDS (C <= kTokPoolMax) and
 // stored once at the end; otherwise a few lanes store them chunk by chunk.
@@ -450,8 +181,8 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
   __shared__ float s_rq[NQ];
   __shared__ float s_sig[WV][NQ];  // per-wave column sums of S
 
-  int t, tile, sl;
-  unit_of_block(blockIdx.x, f.tiles, 1, t, tile, sl);
+  int t, tile;
+  unit_of_block(blockIdx.x, f.tiles, t, tile);
   if (t >= f.T) return;
   const int N = f.N, C = f.C, Q = f.Q;
   const int tok0 = tile * tile_tokens;
@@ -795,8 +526,8 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
   __shared__ float s_sig[2][NQ];    // column sums of S per row group
   __shared__ float s_best[4][RT];   // row maxima of S_nj / |q_j| per column group
 
-  int t, tile, sl;
-  unit_of_block(blockIdx.x, f.tiles, 1, t, tile, sl);
+  int t, tile;
+  unit_of_block(blockIdx.x, f.tiles, t, tile);
   if (t >= f.T) return;
   const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
   const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
@@ -1013,138 +744,276 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
 }
 
 // ---------------------------------------------------------------------------
-// Vector-ALU path
+// Wide queries (bf16, Q > 128)
 // ---------------------------------------------------------------------------
-template <typename In>
-struct Vec;
-template <>
-struct Vec<float> {
-  static constexpr int kN = 4;
-  __device__ static void load(const float* p, float* v) {
-    const f32x4 x = *reinterpret_cast<const f32x4*>(p);
-    v[0] = x[0]; v[1] = x[1]; v[2] = x[2]; v[3] = x[3];
-  }
-};
-template <>
-struct Vec<uint16_t> {
-  static constexpr int kN = 8;
-  __device__ static void load(const uint16_t* p, float* v) {
-    const u32x4 x = *reinterpret_cast<const u32x4*>(p);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) { v[2 * i] = bf16_lo(x[i]); v[2 * i + 1] = bf16_hi(x[i]); }
-  }
-};
+// S has too many columns for one wave's accumulators or for a query stage that
+// waves share, so the columns are dealt to eight waves (16-column tile n * 8 +
+// wave, n < NTW: 128 NTW columns a pass, up to 384) and each stages its own
+// columns' query rows, which no other wave uses, in LDS of its own (loaded
+// straight into the MFMA layout, 16 rows' lines to an instruction, each load
+// took four times the cycles of eight whole lines: 76 against 65 us at Q =
+// 300).  The tile of X is staged for all of them; two chunks of 64 channels at
+// a time, 16-byte units XOR-swizzled by row, X's stage double-buffered with one
+// LDS-only barrier every two chunks.  The loads in flight are the next two
+// chunks of the query and the next four of X, in that order: loads return in
+// order, and a wait for the query must not drain X's, which come from farther.
+// |x|^2, |q_j|^2 and the channel sums are formed from the registers.
+// Sums of products run in chains of four chunks, added up in a second
+// accumulator (one chain of C / 32 steps was three times as far from the 64-bit
+// result).
+// A workgroup owns at most `sub` stretches of 16 MTW tokens of one frame, one
+// after another, with all channels, so a_{t,n} is final here; with sub > 1 (when
+// the partial sums of finer tiles would not fit the scratch) the channel and
+// column sums add up over the stretches in order.  Queries of more than 384
+// tokens take passes over a stretch, channel sums in the first.
+// Bound: LDS, which every wave reads the tile from.  It replaced channel slices
+// with partial scores through memory, dot products on the vector ALU for small
+// frames (Q > 256), and passes of 32 columns over the tile (Q <= 256).
+// wz_relevance at T = 64, 14x14, C = 3584: Q = 130 84 -> 54 us, Q = 300 209 ->
+// 75 us (error against 64 bits 1.3e-7 -> 0.95e-7), Q = 1024 603 -> 221 us; T =
+// 40, 5x5, C = 1024, Q = 300: 1409 -> 23 us.  Four further waves that load X and
+// form the sums leave the contracting ones no registers for the second
+// accumulator (Q = 300 62 us, but three times the error).
+constexpr int kWideWaves = 8;
+constexpr int kWideThreads = kWideWaves * kWave;
 
-template <typename In>
-__global__ __launch_bounds__(256) void k_relevance_valu(int tile_tokens, const VideoArgs<StreamArgs> va) {
+template <int MTW, int NTW>
+__global__ __launch_bounds__(kWideThreads, 2) void k_relevance_wide(int tile_tokens, int sub,
+                                                                    const VideoArgs<StreamArgs> va) {
   const StreamArgs f = va.v[blockIdx.y];
-  const In* __restrict__ X = static_cast<const In*>(f.X);
-  const In* __restrict__ query = static_cast<const In*>(f.query);
-  constexpr int NW = 4;
-  constexpr int V = Vec<In>::kN;
-  constexpr int QB = 16;
-  __shared__ float s_rq[kQMax];
-  __shared__ float s_sig[NW][kQMax];
+  constexpr int ROWS = 64;                    // rows of the stage
+  constexpr int NQ = kWideWaves * 16 * NTW;   // columns of a pass
+  __shared__ __align__(16) u32x4 s_x[2][2][ROWS][8];               // two chunks a buffer
+  __shared__ __align__(16) u32x4 s_q[kWideWaves][2][16 * NTW][8];  // each wave's query rows of two chunks
+  __shared__ float s_pp[2][2][2 * MTW][kTokChunk];                 // per-wave channel sums of a chunk
+  __shared__ float s_xx[ROWS];
+  __shared__ float s_qq[kWideWaves][16 * NTW];
+  __shared__ float s_best[kWideWaves][16 * MTW];  // row maxima of S_nj / |q_j| over a wave's columns
 
-  int t, tile, sl;
-  unit_of_block(blockIdx.x, f.tiles, 1, t, tile, sl);
+  int t, tile;
+  unit_of_block(blockIdx.x, f.tiles, t, tile);
   if (t >= f.T) return;
   const int N = f.N, C = f.C, Q = f.Q;
-  const int tok0 = tile * tile_tokens;
-  const int TM = min(tile_tokens, N - tok0);
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int nvec = C / V;
-  const size_t part = size_t(t) * f.tiles + tile;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int r16 = lane & 15, grp = lane >> 4;  // MFMA layout: row / column, K group
+  const int rb = tid >> 3, lr = lane >> 3, lu = tid & 7;  // load layout: tile row rb, query rows 8 k + lr, 16-byte unit lu
+  const int nch = (C + kTokChunk - 1) / kTokChunk;
+  const int nloop = (nch + 3) / 4 * 4;  // chunks past the end read zeros and store nowhere
+  const int npass = (Q + NQ - 1) / NQ;
+  const int tile0 = tile * tile_tokens, tile1 = min(N, tile0 + tile_tokens);
+  const int step = (tile_tokens + sub - 1) / sub;  // tokens of a stretch, at most 16 MTW
+  const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X) + size_t(t) * N * C;
+  const size_t unit = size_t(t) * f.tiles + tile;
+  const __amdgpu_buffer_rsrc_t pres = make_rsrc_uniform(f.pool_part + unit * C, uint32_t(C) * 4);
+  uint32_t one_lo = kBf16OneLo, one_hi = kBf16OneHi;
+  asm volatile("" : "+v"(one_lo), "+v"(one_hi));  // opaque: keeps them out of inline constants
+  auto row8_sum = [](float v) {  // the 8 lanes of a load-layout row
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0xB1, 0xF, 0xF, false));   // lane ^ 1
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x4E, 0xF, 0xF, false));   // lane ^ 2
+    v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x141, 0xF, 0xF, false));  // 7 - i in 8
+    return v;
+  };
 
-  // 1 / |q_j|
-  for (int j = wave; j < Q; j += NW) {
-    float s = 0.f;
-    for (int v = lane; v < nvec; v += kWave) {
-      float q[V];
-      Vec<In>::load(query + size_t(j) * C + v * V, q);
+  for (int tok0 = tile0; tok0 < tile1; tok0 += step) {
+    const int TM = min(step, tile1 - tok0);
+    const bool first = tok0 == tile0;
+    const __amdgpu_buffer_rsrc_t xres = make_rsrc_uniform(X + size_t(tok0) * C, uint32_t(TM) * C * 2);
+    for (int h = 0; h < npass; ++h) {
+      const int qb = h * NQ;
+      const __amdgpu_buffer_rsrc_t qres =
+          make_rsrc_uniform(static_cast<const uint16_t*>(f.query) + size_t(qb) * C, uint32_t(min(NQ, Q - qb)) * C * 2);
+      // the wave's last tile has columns (uniform over the wave; the others
+      // hardly ever lack them)
+      const bool live = qb + 16 * (kWideWaves * (NTW - 1) + wave) < Q;
+      // (rows past the stretch or the query lie past the end of their buffer and read zeros)
+      const int xoff = rb * C * 2 + 16 * lu;
+      const int qoff = (16 * wave + lr) * C * 2 + 16 * lu, qstep = 16 * kWideWaves * C * 2;
+      auto load_x = [&](int c, u32x4& d) {
+        d = buf_load_u32x4(xres, c * kTokChunk + 8 * lu < C ? xoff + c * kTokChunk * 2 : kOOB);
+      };
+      auto load_q = [&](int c, u32x4 (&d)[NTW][2]) {
+        const int off = c * kTokChunk + 8 * lu < C ? qoff + c * kTokChunk * 2 : kOOB;
 #pragma unroll
-      for (int i = 0; i < V; ++i) s += q[i] * q[i];
-    }
-    s = wave_sum(s);
-    if (lane == 0) {
-      s_rq[j] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
-      if (tile == 0) f.qg_part[size_t(t) * Q + j] = s;
-    }
-  }
-  for (int j = tid; j < NW * kQMax; j += 256) (&s_sig[0][0])[j] = 0.f;
-  __syncthreads();
-
-  for (int r = wave; r < TM; r += NW) {
-    const In* x = X + (size_t(t) * N + tok0 + r) * C;
-    float best = -INFINITY, xn2 = 0.f;
-    for (int j0 = 0; j0 < Q; j0 += QB) {
-      float d[QB];
+        for (int n = 0; n < NTW; ++n)
 #pragma unroll
-      for (int k = 0; k < QB; ++k) d[k] = 0.f;
-      float n2 = 0.f;
-      for (int v = lane; v < nvec; v += kWave) {
-        float xv[V];
-        Vec<In>::load(x + v * V, xv);
+          for (int k = 0; k < 2; ++k) d[n][k] = buf_load_u32x4(qres, off + n * qstep + 8 * k * C * 2);
+      };
+      f32x4 Sacc[MTW][NTW];
+      float qq[NTW][2], xx = 0.f;
 #pragma unroll
-        for (int i = 0; i < V; ++i) n2 += xv[i] * xv[i];
+      for (int n = 0; n < NTW; ++n) {
+        qq[n][0] = qq[n][1] = 0.f;
 #pragma unroll
-        for (int k = 0; k < QB; ++k) {
-          if (j0 + k < Q) {
-            float qv[V];
-            Vec<In>::load(query + size_t(j0 + k) * C + v * V, qv);
+        for (int i = 0; i < MTW; ++i) Sacc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      u32x4 rx[2][2], rq[2][NTW][2];
+      load_x(0, rx[0][0]);
+      load_x(1, rx[0][1]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_q(0, rq[0]);
+      load_q(1, rq[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      load_x(2, rx[1][0]);
+      load_x(3, rx[1][1]);
+      __builtin_amdgcn_sched_barrier(0);
+      for (int c0 = 0; c0 < nloop; c0 += 4) {
+        f32x4 part[MTW][NTW];
+        float qp[NTW][2], xp = 0.f;
 #pragma unroll
-            for (int i = 0; i < V; ++i) d[k] += xv[i] * qv[i];
+        for (int n = 0; n < NTW; ++n) {
+          qp[n][0] = qp[n][1] = 0.f;
+#pragma unroll
+          for (int i = 0; i < MTW; ++i) part[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+          const int c = c0 + 2 * b;
+          // chunks c, c + 1: the tile's rows to the stage, |x|^2 and the channel sums
+#pragma unroll
+          for (int m = 0; m < 2; ++m) {
+            const u32x4 v = rx[b][m];
+            s_x[b][m][rb][lu ^ (rb & 7)] = v;
+            float cs[8];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              xp = dot2(v[e], v[e], xp);
+              cs[2 * e] = dot2(v[e], one_lo, 0.f);
+              cs[2 * e + 1] = dot2(v[e], one_hi, 0.f);
+            }
+            // lane 8 k + lu ends with channel 8 lu + k's sum over the wave's rows
+            const float cw = lane_transpose_sum(cs);
+            if (wave < 2 * MTW) s_pp[b][m][wave][8 * lu + lr] = cw;
+          }
+          asm volatile("" : "+v"(xp));  // not below the reload
+          // the wave's query rows (its reads of the last two chunks are behind it), |q_j|^2
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < NTW; ++n)
+#pragma unroll
+              for (int k = 0; k < 2; ++k) {
+                const u32x4 v = rq[m][n][k];
+                s_q[wave][m][16 * n + 8 * k + lr][lu ^ lr] = v;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) qp[n][k] = dot2(v[e], v[e], qp[n][k]);
+                asm volatile("" : "+v"(qp[n][k]));
+              }
+          __builtin_amdgcn_sched_barrier(0);
+          load_q(c + 2, rq[0]);
+          load_q(c + 3, rq[1]);
+          __builtin_amdgcn_sched_barrier(0);
+          load_x(c + 4, rx[b][0]);
+          load_x(c + 5, rx[b][1]);
+          __builtin_amdgcn_sched_barrier(0);
+          lds_barrier();  // the two chunks of X staged; the two before them no longer read
+          // their channel sums, the waves' added in wave order by waves 0 and 1
+          // (every lane stores, most past the end: the count of memory
+          // operations in flight stays the same on every path)
+          float v = 0.f;
+          const int ch = (c + wave) * kTokChunk + lane;
+          const int off = (h == 0 && wave < 2 && ch < C) ? ch * 4 : kOOB;
+          if (wave < 2) {
+#pragma unroll
+            for (int w = 0; w < 2 * MTW; ++w) v += s_pp[b][wave][w][lane];
+            if (!first) v = buf_load_f32(pres, off) + v;
+          }
+          buf_store_f32(v, pres, off);
+#pragma unroll
+          for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int st = 0; st < 2; ++st) {
+              const int u = (4 * st + grp) ^ (r16 & 7);  // unit 4 st + grp of a row of either stage
+              u32x4 A[MTW];
+#pragma unroll
+              for (int i = 0; i < MTW; ++i) A[i] = s_x[b][m][16 * i + r16][u];
+#pragma unroll
+              for (int n = 0; n < NTW; ++n) {
+                if (n < NTW - 1 || live) {
+                  const bf16x8 B = __builtin_bit_cast(bf16x8, s_q[wave][m][16 * n + r16][u]);
+#pragma unroll
+                  for (int i = 0; i < MTW; ++i)
+                    part[i][n] =
+                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, A[i]), B, part[i][n], 0, 0, 0);
+                }
+              }
+            }
+        }
+        xx += xp;
+#pragma unroll
+        for (int n = 0; n < NTW; ++n) {
+          qq[n][0] += qp[n][0];
+          qq[n][1] += qp[n][1];
+#pragma unroll
+          for (int i = 0; i < MTW; ++i) Sacc[i][n] += part[i][n];
+        }
+      }
+      if (h == 0) {
+        const float v = row8_sum(xx);
+        if (lu == 0) s_xx[rb] = v;
+      }
+#pragma unroll
+      for (int n = 0; n < NTW; ++n)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const float v = row8_sum(qq[n][k]);
+          if (lu == 0) s_qq[wave][16 * n + 8 * k + lr] = v;
+        }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // (one wave's own LDS, in program order)
+      __builtin_amdgcn_wave_barrier();
+      // the wave's columns: sigma_j (rows past the stretch hold zeros), |q_j|^2
+      // and its row maxima of S_nj / |q_j|
+      float rqn[NTW];
+#pragma unroll
+      for (int n = 0; n < NTW; ++n) {
+        const int j = qb + 16 * (kWideWaves * n + wave) + r16;
+        float v = 0.f;
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) v += (Sacc[i][n][0] + Sacc[i][n][1]) + (Sacc[i][n][2] + Sacc[i][n][3]);
+        v = row_sum4(v);
+        const float qv = s_qq[wave][16 * n + r16];
+        rqn[n] = qv > 0.f ? 1.0f / sqrtf(qv) : 0.f;
+        if (j < Q && lane < 16) {
+          float* sig = f.sig_part + unit * Q + j;
+          *sig = first ? v : *sig + v;
+          if (tile == 0 && first) f.qg_part[size_t(t) * Q + j] = qv;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < MTW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float best = -INFINITY;
+#pragma unroll
+          for (int n = 0; n < NTW; ++n)
+            if (qb + 16 * (kWideWaves * n + wave) + r16 < Q) best = fmaxf(best, Sacc[i][n][e] * rqn[n]);
+          best = fmaxf(best, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(best), 0xB1, 0xF, 0xF, false)));
+          best = fmaxf(best, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(best), 0x4E, 0xF, 0xF, false)));
+          best = fmaxf(best, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(best), 0x141, 0xF, 0xF, false)));
+          best = fmaxf(best, __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(best), 0x140, 0xF, 0xF, false)));
+          if (r16 == e) {
+            float& out = s_best[wave][16 * i + 4 * grp + e];
+            out = h == 0 ? best : fmaxf(out, best);
           }
         }
-      }
-      if (j0 == 0) xn2 = wave_sum(n2);
-#pragma unroll
-      for (int k = 0; k < QB; ++k) {
-        if (j0 + k < Q) {
-          const float s = wave_sum(d[k]);
-          best = fmaxf(best, s * s_rq[j0 + k]);
-          if (lane == 0) s_sig[wave][j0 + k] += s;
-        }
-      }
     }
-    if (lane == 0) {
-      const float xn = sqrtf(xn2);
-      f.tok_score[size_t(t) * N + tok0 + r] = xn > 0.f ? best / xn : 0.f;
+    lds_barrier();  // s_best and s_xx complete (rewritten behind at least one more barrier)
+    // a_{t,n} = max_j S_nj / (|q_j| |x_n|), the waves' maxima in order
+    if (tid < TM) {
+      float best = s_best[0][tid];
+#pragma unroll
+      for (int w = 1; w < kWideWaves; ++w) best = fmaxf(best, s_best[w][tid]);
+      const float xn = sqrtf(s_xx[tid]);
+      f.tok_score[size_t(t) * N + tok0 + tid] = xn > 0.f ? best / xn : 0.f;
     }
-  }
-
-  // channel sums of the tile (tokens in order)
-  for (int v = tid; v < nvec; v += 256) {
-    float acc[V];
-#pragma unroll
-    for (int i = 0; i < V; ++i) acc[i] = 0.f;
-    for (int r = 0; r < TM; ++r) {
-      float xv[V];
-      Vec<In>::load(X + (size_t(t) * N + tok0 + r) * C + v * V, xv);
-#pragma unroll
-      for (int i = 0; i < V; ++i) acc[i] += xv[i];
-    }
-#pragma unroll
-    for (int i = 0; i < V; ++i) f.pool_part[part * C + v * V + i] = acc[i];
-  }
-  __syncthreads();
-  for (int j = tid; j < Q; j += 256) {
-    float s = 0.f;
-    for (int w = 0; w < NW; ++w) s += s_sig[w][j];
-    f.sig_part[part * Q + j] = s;
   }
 }
 
-#ifndef WZ_REL_RING
-#define WZ_REL_RING 4  // X prefetch depth in 32-channel steps (MFMA-layout path)
-#endif
-
-template <int NTG>
-void launch_mfma(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
-  hipLaunchKernelGGL((k_relevance_mfma<NTG, WZ_REL_RING>), dim3(pl.grid, V), dim3(pl.threads), 0, s, pl.tile_tokens,
-                     pl.kc, va);
+template <int MTW>
+void launch_wide_rows(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
+  const dim3 grid(pl.grid, V), block(kWideThreads);
+  if (pl.ntw == 2) hipLaunchKernelGGL((k_relevance_wide<MTW, 2>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
+  else hipLaunchKernelGGL((k_relevance_wide<MTW, 3>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
 }
 
 // LDS of a token-tiled workgroup without the gathered channel sums.
@@ -1189,8 +1058,8 @@ void launch_tok(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipSt
   if (va.v[0].groups > 1) {
     launch_tok_mode<In, NTG, IPC, kTokGroups>(pl, va, V, s);
   } else if (va.v[0].Q > 16 * NTG) {
-    // the plan takes two query tiles for passes (checked by the caller)
-    if constexpr (NTG == 2) launch_tok_mode<In, NTG, IPC, kTokPasses>(pl, va, V, s);
+    // fp32 inputs; the plan takes two query tiles for passes (checked by the caller)
+    if constexpr (NTG == 2 && sizeof(In) == 4) launch_tok_mode<In, NTG, IPC, kTokPasses>(pl, va, V, s);
   } else {
     launch_tok_mode<In, NTG, IPC, kTokOne>(pl, va, V, s);
   }
@@ -1220,10 +1089,7 @@ void launch_tok_shape(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V,
 
 RelKind relevance_kind(const wz_config& c) {
   if (c.in_dtype != WZ_BF16) return kRelTok;  // passes of 32 columns above 64 query tokens
-  if (c.Q > 64 && c.Q <= kWgQMax) return kRelWg;
-  if (c.Q <= kTokQMax) return kRelTok;
-  // two 16-row MFMA tiles per wave, at least 2 waves: frames of at least 49 tokens
-  return c.H * c.W >= 49 ? kRelMfma : kRelValu;
+  return c.Q <= 64 ? kRelTok : c.Q <= kWgQMax ? kRelWg : kRelWide;
 }
 
 hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void* query, float* tok_score,
@@ -1241,21 +1107,21 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     for (int e = 0; e < V; ++e) {
       const int q0 = e * G, n = std::min(G, vs.V - q0);
       const Workspace w = advance(ws, q0 * vs.ws);
-      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.s_part, w.g_part, w.qg_part, w.sig_part, w.pool_part,
-                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, qpad(c.Q * n), pl.tiles,
-                           pl.slices, n, c.Q, vs.ws};
+      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.qg_part, w.sig_part, w.pool_part,
+                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, pl.tiles, n,
+                           c.Q, vs.ws};
     }
   } else {
     for (int v = 0; v < vs.V; ++v) {
       const Workspace w = advance(ws, v * vs.ws);
-      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.s_part, w.g_part, w.qg_part,
-                           w.sig_part, w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q,
-                           qpad(c.Q), pl.tiles, pl.slices};
+      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.qg_part, w.sig_part,
+                           w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q,
+                           pl.tiles};
     }
   }
   if (pl.kind == kRelTok) {
     // columns beyond the query tiles are served by passes of two tiles only
-    if (va.v[0].Q > 16 * pl.ntg && (pl.ntg != 2 || va.v[0].groups > 1)) return hipErrorInvalidValue;
+    if (va.v[0].Q > 16 * pl.ntg && (pl.ntg != 2 || va.v[0].groups > 1 || c.in_dtype == WZ_BF16)) return hipErrorInvalidValue;
     if (c.in_dtype == WZ_BF16) launch_tok_shape<uint16_t>(pl, va, V, s);
     else launch_tok_shape<float>(pl, va, V, s);
   } else if (pl.kind == kRelWg) {
@@ -1264,12 +1130,14 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
       hipLaunchKernelGGL((k_relevance_wg<1>), dim3(pl.grid, V), dim3(kWgWaves * 64), 0, s, pl.tile_tokens, va);
     else
       hipLaunchKernelGGL((k_relevance_wg<2>), dim3(pl.grid, V), dim3(kWgWaves * 64), 0, s, pl.tile_tokens, va);
-  } else if (pl.kind == kRelMfma) {
-    // queries of more than 32 tokens take several passes of 32 over the slice:
-    // wider query groups no longer fit the accumulators in registers
-    launch_mfma<2>(pl, va, V, s);
   } else {
-    hipLaunchKernelGGL((k_relevance_valu<uint16_t>), dim3(pl.grid, V), dim3(pl.threads), 0, s, pl.tile_tokens, va);
+    if (va.v[0].groups > 1 || pl.mt > 4) return hipErrorInvalidValue;
+    switch (pl.mt) {
+      case 1: launch_wide_rows<1>(pl, va, V, s); break;
+      case 2: launch_wide_rows<2>(pl, va, V, s); break;
+      case 3: launch_wide_rows<3>(pl, va, V, s); break;
+      default: launch_wide_rows<4>(pl, va, V, s); break;
+    }
   }
   return hipGetLastError();
 }
