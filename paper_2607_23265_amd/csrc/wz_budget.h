@@ -6,9 +6,9 @@
 //
 // The budget is a few fp64 operations per frame, so it runs in ONE workgroup
 // with every array in LDS, or in one wave: up to T = 64 with every value in
-// registers (budget_wave_compute), up to T = 256 with four frames per lane,
-// also in registers (budget_wave_slots; budget_body with NT = 64 keeps the
-// same layout in LDS, for the filter-bank bases); 1024 threads beyond.
+// registers (budget_wave_compute), up to T = 512 with up to eight frames per
+// lane, also in registers (budget_wave_slots; budget_body with NT = 64 keeps
+// the same layout in LDS, for the filter-bank bases); 1024 threads beyond.
 // Steps:
 //   gamma  = min-max(delta) over all T frames (0 if all equal);
 //   M      = {0} U {t >= 1 : delta_t >= tau}, compacted in temporal order;
@@ -597,7 +597,7 @@ __device__ void budget_wave_compute(double d, double r, int T, int N, long long 
 }
 
 // ---------------------------------------------------------------------------
-// T <= TV (TV = 64 SL, at most 256): one wave, frame t and retained position
+// T <= TV (TV = 64 SL, at most 512): one wave, frame t and retained position
 // i in slot t / 64 (i / 64) of lane t % 64 (i % 64), every value in
 // registers except each level's detail coefficients (LDS); the compaction
 // to the retained positions and the way back go through LDS only when the
@@ -611,7 +611,7 @@ __device__ void budget_wave_slots(const float* __restrict__ rel, const float* __
                                   long long B, int levels, float tau, int32_t* __restrict__ budget,
                                   int32_t* __restrict__ offset, float* __restrict__ rel_rect) {
   constexpr int SL = TV / kWave;
-  static_assert(TV % kWave == 0 && SL >= 1 && SL <= 4, "one to four slots per lane");
+  static_assert(TV % kWave == 0 && SL >= 1 && SL <= 8, "one to eight slots per lane");
   const double inv_sqrt2 = 0.70710678118654752440;
   const int lane = threadIdx.x & 63;
   const uint64_t below = (1ull << lane) - 1ull;  // lanes before this one

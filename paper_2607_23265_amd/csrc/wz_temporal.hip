@@ -1,8 +1,7 @@
 // Stage 2 on its own: the Wavelet Temporal Allocator (gate and frame
 // filter of Sec. 3.2.2; Sec. 3.2.3, Eq. (9)-(11)) and the integer frame budgets (Sec. 3.2.4, Eq. (16)
-// under Eq. (5)) in ONE workgroup: one wave up to T = 256 (every value in
-// registers up to 64 frames, four frames per lane in LDS above), 1024
-// threads beyond.  The arithmetic lives in wz_budget.h, which the fused
+// under Eq. (5)) in ONE workgroup: one wave up to T = 512 (up to eight frames
+// per lane, in registers), 1024 threads beyond.  The arithmetic lives in wz_budget.h, which the fused
 // selection and gather kernel runs too.  With a db4 or bior4.4 temporal basis
 // the LDS version runs at every T, with 256 threads from 65 to 256 frames.
 #include "wz_budget.h"
@@ -28,7 +27,7 @@ __global__ __launch_bounds__(NT) void k_budget(const VideoArgs<BudgetArgs> va, i
     budget_body<NT, TV>(a.rel, a.delta, T, N, B, levels, tau, a.budget, a.offset, a.rel_rect, &bank);
   else if constexpr (NT == kWave && TV == kWave)
     budget_wave_body(a.rel, a.delta, T, N, B, levels, tau, a.budget, a.offset, a.rel_rect);
-  else if constexpr (NT == kWave && TV <= 4 * kWave)
+  else if constexpr (NT == kWave && TV <= 8 * kWave)
     budget_wave_slots<TV>(a.rel, a.delta, T, N, B, levels, tau, a.budget, a.offset, a.rel_rect);
   else
     budget_body<NT, TV>(a.rel, a.delta, T, N, B, levels, tau, a.budget, a.offset, a.rel_rect);
@@ -57,6 +56,9 @@ hipError_t launch_budget(const wz_config& c, const float* frame_rel, const float
   if (c.T <= 64) launch_k<kWave, 64>(c, va, vs.V, s);
   else if (c.T <= 128 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 128>(c, va, vs.V, s);
   else if (c.T <= 256 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 256>(c, va, vs.V, s);
+  // (one wave's lane swaps against a workgroup's barriers at every reduction:
+  // a T = 512, 8x8, C = 3584 call 98.9 -> 81.6 us, T = 300 81.6 -> 66.9 us)
+  else if (c.T <= 512 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 512>(c, va, vs.V, s);
   else if (c.T <= 256) launch_k<256, 256>(c, va, vs.V, s);
   else launch_k<1024, kTMax>(c, va, vs.V, s);
   return hipGetLastError();
