@@ -77,6 +77,7 @@ struct FilterArgs {
   int32_t* out_index;       // [B]
   long long B;
   int T, H, W, C, levels;
+  int parts;                // workgroups per frame of the row kernel
   float lam, tau;
 };
 static_assert(sizeof(VideoArgs<FilterArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
   constexpr int RW = KR / kFWaves;  // rows a wave contracts
   const FilterArgs& f = va.v[blockIdx.y];
   constexpr int SLICE = filter_slice(sizeof(In) == 2);
-  const int S = ROWS ? 1 : (f.C + SLICE - 1) / SLICE;
+  const int S = ROWS ? f.parts : (f.C + SLICE - 1) / SLICE;
   const int b = blockIdx.x, xcd = b % kXcds, slot = b / kXcds;
   const int t = (slot / S) * kXcds + xcd, sl = slot % S;
   if (t >= f.T) return;  // whole workgroup
@@ -404,7 +405,7 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
   const __amdgpu_buffer_rsrc_t xres = make_rsrc(static_cast<const In*>(f.X) + size_t(t) * N * C, uint32_t(N) * rb);
   const int xoff = vok ? v * 8 * int(sizeof(In)) : kOOB;
 
-  for (int c0 = 0; c0 < nt; c0 += KR) {
+  for (int c0 = ROWS ? sl * KR : 0; c0 < nt; c0 += ROWS ? S * KR : KR) {
     // ---- 3a. B1_i(w') = sum_j (1 - G_ij) E'_j(w'), B2_i(w') = sum_j G_ij P'_j(w')
     // for the chunk's rows, i over the coefficients reaching the row's h ----
     for (int q = tid; q < KR * kMaxAct * W; q += kFThreads) {
@@ -816,10 +817,17 @@ int filter_rows(int H, int W, int F, bool mfma, int det_levels = 0) {
   return 0;
 }
 
-// the row kernel: one workgroup per frame
+// workgroups per frame of the row kernel (V videos at once): as many as fill
+// the CUs, one to a CU by its LDS; each repeats the frame's setup, so no more
+// (C = 1152, 27x27, a call with one and with this many: T = 48 103.9 -> 74.1
+// us, T = 96 134.7 -> 127.3 us; twice as many at T = 96: 133.7 us).
+int filter_row_parts(const wz_config& c, int V) {
+  return std::max(1, std::min(4, kCUs / ((c.T + kXcds - 1) / kXcds * kXcds * V)));
+}
+// the row kernel: parts workgroups per frame, each every parts-th chunk of rows
 void launch_filter_rows(const wz_config& c, const VideoArgs<FilterArgs>& va, int V, const Bank& bank, int det_levels,
                         hipStream_t s) {
-  const dim3 grid(unsigned((c.T + kXcds - 1) / kXcds * kXcds), V), block(kFThreads);
+  const dim3 grid(unsigned((c.T + kXcds - 1) / kXcds * kXcds * va.v[0].parts), V), block(kFThreads);
   const int kr = filter_rows(c.H, c.W, bank.F, true, det_levels);
   const size_t lds = filter_lds(c.H, c.W, bank.F, kr, true, det_levels).bytes;
   if (kr == 32) hipLaunchKernelGGL((k_filter_assign<uint16_t, uint16_t, 32, true>), grid, block, lds, s, va, bank);
@@ -907,6 +915,7 @@ hipError_t launch_filter_assign(const wz_config& c, const void* X, const float* 
     a.W = c.W;
     a.C = c.C;
     a.levels = c.levels;
+    a.parts = filter_row_parts(c, vs.V);
     a.lam = c.lambda_;
     a.tau = c.tau;
   }
