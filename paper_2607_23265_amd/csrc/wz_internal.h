@@ -52,13 +52,52 @@ constexpr size_t kScratchBytes = size_t(32) << 20;
 //   kRelTok  fp32; bf16, Q <= 64: token tiles, each wave a channel stripe with
 //            its own LDS-transposed MFMA (fp32 above 64 query tokens: passes
 //            of 32 columns per tile);
-//   kRelWg   bf16, 64 < Q <= 128: the workgroup's waves share each channel
-//            chunk of the tile and the query in LDS, each wave some 16-row
-//            tiles against every column;
+//   kRelWg   bf16, 64 < Q <= 128 (and 32 < Q <= 64, see relevance_kind): the
+//            workgroup's waves share each channel chunk of the tile and the
+//            query in LDS, each wave some 16-row tiles against every column;
 //   kRelWide bf16, Q > 128: the waves split the query's columns and share
 //            each chunk of the tile in LDS.
 enum RelKind { kRelTok = 0, kRelWg = 1, kRelWide = 2 };
-RelKind relevance_kind(const wz_config& c);
+
+// Token tiles per frame of at most `cap` tokens for `slots` workgroups running
+// at once: the count (tiles of 16 tokens and up) with the fewest rows of X and
+// query a slot loads over its turns, the smaller count on a tie.
+inline int rel_tiles(const wz_config& c, int cap, int slots, int qrows) {
+  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds;
+  const int lo = (N + cap - 1) / cap, hi = std::max(lo, (N + 15) / 16);
+  // fp32 inputs: tiles finer than 32 tokens (whose channel and column sums
+  // the workspace holds, T * tiles * (C + Q) floats) only while those stay
+  // under half of the allocation-free call's 32 MiB
+  const bool f32 = c.in_dtype != WZ_BF16;
+  long best = -1;
+  int tiles = lo;
+  for (int k = lo; k <= hi; ++k) {
+    if (f32 && k > lo && k > (N + 31) / 32 && (long long)c.T * k * (c.C + c.Q) * 4 > (16LL << 20)) break;
+    const long cost = long((long(tr) * k + slots - 1) / slots) * ((N + k - 1) / k + qrows);
+    if (best < 0 || cost < best) best = cost, tiles = k;
+  }
+  return tiles;
+}
+
+inline RelKind relevance_kind(const wz_config& c) {
+  if (c.in_dtype != WZ_BF16 || c.Q <= 32) return kRelTok;  // (fp32: passes of 32 columns above 64 query tokens)
+  if (c.Q > 64) return c.Q <= 128 ? kRelWg : kRelWide;
+  // 33 to 64 query tokens: channel stripes leave one workgroup to a CU, whose
+  // turns do not overlap (about 4 us, and 3 us for each eight 64-channel
+  // chunks); the shared tiles leave two, with a barrier a chunk (0.9 us; tiles
+  // of more than 64 tokens 1.45 us).  At Q = 48, channel stripes against shared
+  // tiles: T = 512, 14x14, C = 768 74.2 / 44.4 us; T = 256, 27x27, C = 1152
+  // 163.1 / 121.9; T = 200, 14x14, C = 2560 67.9 / 58.7; T = 150, 20x20, C =
+  // 1536 68.7 / 67.5; T = 512, 8x8, C = 3584 54.7 / 62.4; T = 110, 12x12, C =
+  // 4096 44.3 / 61.5.  Finer tiles than the stripes' would also take more
+  // workspace.
+  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, chunks = (c.C + 63) / 64;
+  const int kt = rel_tiles(c, 64, kCUs, 64), kw = rel_tiles(c, 128, 2 * kCUs, 64);
+  const long turns_t = (long(tr) * kt + kCUs - 1) / kCUs, turns_w = (long(tr) * kw + 2 * kCUs - 1) / (2 * kCUs);
+  const long tok = turns_t * (80 + 60 * ((chunks + 7) / 8));                           // in 0.05 us
+  const long wg = turns_w * chunks * ((N + kw - 1) / kw <= 64 ? 18 : 29) + 60;
+  return kw <= kt && wg < tok ? kRelWg : kRelTok;
+}
 
 struct RelPlan {
   RelKind kind;
@@ -78,43 +117,20 @@ inline RelPlan relevance_plan(const wz_config& c) {
   RelPlan p{};
   p.kind = relevance_kind(c);
   if (p.kind == kRelTok) {
-    // tiles of 16 to 64 tokens with every channel, one slice.  A workgroup
-    // fills a CU's LDS, so a CU runs (workgroups / CUs rounded up) of them one
-    // after another, each loading its tile's tokens and the query's 16-row
-    // tiles: take the tile count with the fewest rows loaded per CU, the
-    // smaller count on a tie
-    const int tr = (c.T + kXcds - 1) / kXcds * kXcds;
+    // tiles of 16 to 64 tokens with every channel.  A workgroup fills a CU's
+    // LDS, so a CU runs (workgroups / CUs rounded up) of them one after
+    // another, each loading its tile's tokens and the query's 16-row tiles;
     // query tiles: 1, 2 or 4 of 16 columns; above 64 columns, passes of 32
     const int nq = c.Q <= 16 ? 16 : c.Q <= 32 ? 32 : c.Q <= 64 ? 64 : 32;
-    const int lo = (N + 63) / 64, hi = std::max(lo, (N + 15) / 16);
-    // fp32 inputs: tiles finer than 32 tokens (whose channel and column sums
-    // the workspace holds, T * tiles * (C + Q) floats) only while those stay
-    // under half of the allocation-free call's 32 MiB
-    const bool f32 = c.in_dtype != WZ_BF16;
-    long best = -1;
-    for (int k = lo; k <= hi; ++k) {
-      if (f32 && k > lo && k > (N + 31) / 32 && (long long)c.T * k * (c.C + c.Q) * 4 > (16LL << 20)) break;
-      const int rows = (N + k - 1) / k + nq;
-      const long cost = long((long(tr) * k + kCUs - 1) / kCUs) * rows;
-      if (best < 0 || cost < best) best = cost, p.tiles = k;
-    }
+    p.tiles = rel_tiles(c, 64, kCUs, nq);
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.ipc = (p.tile_tokens + 7) / 8;
     p.ntg = nq / 16;
   } else if (p.kind == kRelWg) {
-    // tiles of at most 128 tokens; two workgroups share a CU.  Every
-    // workgroup streams its tile's rows and the whole query through LDS:
-    // take the tile count with the fewest rows streamed per CU slot, the
-    // smaller count on a tie
-    const int tr = (c.T + kXcds - 1) / kXcds * kXcds;
-    p.ntg = c.Q <= 16 ? 1 : c.Q <= 32 ? 2 : c.Q <= 64 ? 4 : 8;
-    const int lo = (N + 127) / 128, hi = std::max(lo, (N + 15) / 16);
-    long best = -1;
-    for (int k = lo; k <= hi; ++k) {
-      const int rows = (N + k - 1) / k + 16 * p.ntg;
-      const long cost = long((long(tr) * k + 2 * kCUs - 1) / (2 * kCUs)) * rows;
-      if (best < 0 || cost < best) best = cost, p.tiles = k;
-    }
+    // tiles of at most 128 tokens; two workgroups share a CU.  Every workgroup
+    // streams its tile's rows and the whole query through LDS
+    p.ntg = c.Q <= 64 ? 4 : 8;
+    p.tiles = rel_tiles(c, 128, 2 * kCUs, 16 * p.ntg);
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.rtw = p.tile_tokens <= 64 ? 1 : 2;
   } else {

@@ -10,7 +10,8 @@
 // Three decompositions, each with every channel in a workgroup:
 //  * token tiles (fp32 inputs; bf16, Q <= 64): a workgroup owns up to 64 tokens
 //    of a frame, its waves split the channels;
-//  * shared token tiles (bf16, 64 < Q <= 128): the waves share each chunk of
+//  * shared token tiles (bf16, 64 < Q <= 128, and 32 < Q <= 64 where a CU would
+//    take turns of the former): the waves share each chunk of
 //    the tile and of the query in LDS and split S;
 //  * wide queries (bf16, Q > 128): the waves split the query's columns, which
 //    they read from L2, and share the tile in LDS.
@@ -488,7 +489,7 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
 }
 
 // ---------------------------------------------------------------------------
-// Workgroup-shared token tiles (bf16, 64 < Q <= 128)
+// Workgroup-shared token tiles (bf16, 64 < Q <= 128; 32 < Q <= 64 by relevance_kind's rule)
 // ---------------------------------------------------------------------------
 // With a wide query, per-wave channel stripes (above) would stage the query
 // once per wave and add every wave's partial S through LDS.  Here the eight
@@ -504,17 +505,14 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
 // flight in registers.  The row maxima and column sums of S are combined
 // across the waves through LDS at the end, in a fixed order.  Two
 // workgroups share a CU.
-constexpr int kWgQMax = 128;  // query tokens of the workgroup-shared path
 constexpr int kWgWaves = 8;
-constexpr int kWgNQ = 128;    // query rows the stage holds (eight 16-column tiles)
 
-template <int RTW>
+template <int RTW, int NTW>
 __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_tokens, const VideoArgs<StreamArgs> va) {
   const StreamArgs f = va.v[blockIdx.y];
   constexpr int RT = 64 * RTW;                 // tile rows the stage holds
-  constexpr int NQ = kWgNQ;
+  constexpr int NQ = 64 * NTW;                 // query rows the stage holds
   constexpr int MTW = 2 * RTW;                 // 16-row tiles per wave
-  constexpr int NTW = 2;                       // 16-column tiles per wave
   constexpr int XR = RT / 64;                  // tile rows each thread loads per chunk
   constexpr int QR = NQ / 64;                  // query rows each thread loads per chunk
   constexpr int D = 2 + (RTW == 1);            // chunks of loads in flight
@@ -572,6 +570,19 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
   for (int k = 0; k < XR; ++k) xx[k] = 0.f;
 #pragma unroll
   for (int k = 0; k < QR; ++k) qq[k] = 0.f;
+  // with one column tile a wave, sums of products run in chains of D chunks,
+  // added up in second accumulators (as short as the channel stripes' chains)
+  constexpr bool CHAIN = NTW == 1;
+  f32x4 Ssum[CHAIN ? MTW : 1];
+  float xsum[XR], qsum[QR];
+  if constexpr (CHAIN) {
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) Ssum[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int k = 0; k < XR; ++k) xsum[k] = 0.f;
+#pragma unroll
+    for (int k = 0; k < QR; ++k) qsum[k] = 0.f;
+  }
   uint32_t one_lo = kBf16OneLo, one_hi = kBf16OneHi;
   asm volatile("" : "+v"(one_lo), "+v"(one_hi));  // opaque: keeps them out of inline constants
 
@@ -672,6 +683,25 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
       pool_out(c);
       contract(c);
     }
+    if constexpr (CHAIN) {
+#pragma unroll
+      for (int i = 0; i < MTW; ++i) {
+        Ssum[i] += Sacc[i][0];
+        Sacc[i][0] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int k = 0; k < XR; ++k) xsum[k] += xx[k], xx[k] = 0.f;
+#pragma unroll
+      for (int k = 0; k < QR; ++k) qsum[k] += qq[k], qq[k] = 0.f;
+    }
+  }
+  if constexpr (CHAIN) {
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) Sacc[i][0] = Ssum[i];
+#pragma unroll
+    for (int k = 0; k < XR; ++k) xx[k] = xsum[k];
+#pragma unroll
+    for (int k = 0; k < QR; ++k) qq[k] = qsum[k];
   }
 
   // ---- epilogue ----
@@ -1087,11 +1117,6 @@ void launch_tok_shape(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V,
 
 }  // namespace
 
-RelKind relevance_kind(const wz_config& c) {
-  if (c.in_dtype != WZ_BF16) return kRelTok;  // passes of 32 columns above 64 query tokens
-  return c.Q <= 64 ? kRelTok : c.Q <= kWgQMax ? kRelWg : kRelWide;
-}
-
 hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void* query, float* tok_score,
                                    const Workspace& ws, hipStream_t s, const Videos& vs) {
   RelPlan pl = relevance_plan(c);
@@ -1125,11 +1150,12 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     if (c.in_dtype == WZ_BF16) launch_tok_shape<uint16_t>(pl, va, V, s);
     else launch_tok_shape<float>(pl, va, V, s);
   } else if (pl.kind == kRelWg) {
-    if (va.v[0].groups > 1 || va.v[0].Q > kWgNQ) return hipErrorInvalidValue;
-    if (pl.rtw == 1)
-      hipLaunchKernelGGL((k_relevance_wg<1>), dim3(pl.grid, V), dim3(kWgWaves * 64), 0, s, pl.tile_tokens, va);
-    else
-      hipLaunchKernelGGL((k_relevance_wg<2>), dim3(pl.grid, V), dim3(kWgWaves * 64), 0, s, pl.tile_tokens, va);
+    if (va.v[0].groups > 1 || va.v[0].Q > 16 * pl.ntg) return hipErrorInvalidValue;
+    const dim3 grid(pl.grid, V), block(kWgWaves * 64);
+    if (pl.ntg == 4 && pl.rtw == 1) hipLaunchKernelGGL((k_relevance_wg<1, 1>), grid, block, 0, s, pl.tile_tokens, va);
+    else if (pl.ntg == 4) hipLaunchKernelGGL((k_relevance_wg<2, 1>), grid, block, 0, s, pl.tile_tokens, va);
+    else if (pl.rtw == 1) hipLaunchKernelGGL((k_relevance_wg<1, 2>), grid, block, 0, s, pl.tile_tokens, va);
+    else hipLaunchKernelGGL((k_relevance_wg<2, 2>), grid, block, 0, s, pl.tile_tokens, va);
   } else {
     if (va.v[0].groups > 1 || pl.mt > 4) return hipErrorInvalidValue;
     switch (pl.mt) {
