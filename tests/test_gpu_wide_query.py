@@ -70,3 +70,23 @@ def test_stretches_within_the_scratch():
     torch.cuda.synchronize()
     for got, want, what in ((a, torch.cat(a64), "a"), (r, (pn @ qn.t()).amax(1), "r"), (d, d64, "delta")):
         assert G.within(got.cpu().numpy(), want.cpu().numpy(), G.TOL_F32_IN, what)
+
+
+@pytest.mark.parametrize("T,H,W,C,Q", [(3, 5, 5, 264, 300), (9, 6, 8, 72, 700), (2, 1, 1, 8, 1024)])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf")])
+def test_infinity_in_a_small_frame(T, H, W, C, Q, value):
+    """Frames of fewer than 49 tokens with more than 256 query tokens: an infinite value stays in its own channel's sum
+    (the other channel of its pair does not become NaN), so r and delta are those of the same values in fp32."""
+    g = torch.Generator().manual_seed(T * 1000 + Q)
+    X = torch.randn(T, H, W, C, generator=g).bfloat16()
+    q = (torch.randn(Q, C, generator=g) / C ** 0.5).bfloat16()
+    X[0, 0, 0, 2] = value
+    X[-1, -1, -1, 5] = value
+    p = dict(T=T, H=H, W=W, C=C, Q=Q, B=1)
+    a, r, d = wz.relevance(wz.Problem(in_dtype=wz.WZ_BF16, **p), X.to(DEV), q.to(DEV))
+    a32, r32, d32 = wz.relevance(wz.Problem(in_dtype=wz.WZ_F32, **p), X.float().to(DEV), q.float().to(DEV))
+    torch.cuda.synchronize()
+    for got, want, what in ((a, a32, "a"), (r, r32, "r"), (d, d32, "delta")):
+        got, want = got.cpu().numpy(), want.cpu().numpy()
+        assert np.array_equal(np.isnan(got), np.isnan(want)), what
+        assert G.within(np.nan_to_num(got), np.nan_to_num(want), G.TOL_F32_IN, what)
