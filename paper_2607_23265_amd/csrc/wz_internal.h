@@ -99,6 +99,44 @@ inline RelKind relevance_kind(const wz_config& c) {
   return kw <= kt && wg < tok ? kRelWg : kRelTok;
 }
 
+// Workspace bytes at `tiles` token tiles a frame (see workspace_layout).
+inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split);
+
+// Token tiles per frame of kRelWide: of 16 to 64 tokens, or of up to 256 in
+// stretches of at most 64.  Per 64 channels a stretch's MFMAs take as long as
+// 16-row tiles x column tiles, its query reads from L2 as long as four 16-row
+// tiles do: take the count with the least of their sum over a CU's turns, the
+// smaller count on a tie.
+inline int wide_tiles(const wz_config& c) {
+  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, hi = (N + 15) / 16;
+  auto cost = [&](int k) {
+    const int tt = (N + k - 1) / k, sub = (tt + 63) / 64, rows = ((tt + sub - 1) / sub + 15) / 16 * 16;
+    return long((long(tr) * k + kCUs - 1) / kCUs) * sub * (rows + 64);
+  };
+  int tiles = (N + 63) / 64;
+  for (int k = tiles + 1; k <= hi; ++k)
+    if (cost(k) < cost(tiles)) tiles = k;
+  // The tiles' channel and column sums are the workspace's largest part.  Where
+  // they do not fit the allocation-free call's scratch, the cheapest count that
+  // does (with the filter-bank operator rows, else without), if its cost is not
+  // too far up; otherwise the caller's workspace holds the finer tiles.  The
+  // line: a quarter more up to 256 query tokens (wz_relevance, T = 260, 14x14,
+  // C = 8192, Q = 130: passes of 32 columns 715 us, tiles of 256 tokens, at 1.6
+  // times the cost, 809, of 98 tokens, at 1.2 times, 610; T = 4, 64x64, C =
+  // 32768, Q = 300: 2305 us in tiles of 256 tokens on a quarter of the chip, of
+  // 128 tokens 1346); half more above, where the scratch has always held tiles
+  // of 256 tokens up to C = 1024 (at most 1.43 times the cost there).
+  const long pct = c.Q <= 256 ? 125 : 150;
+  for (const bool split : {true, false}) {
+    if (workspace_bytes_at(c, tiles, split) <= kScratchBytes) break;
+    int fit = 0;
+    for (int k = (N + 255) / 256; k <= hi && workspace_bytes_at(c, k, split) <= kScratchBytes; ++k)
+      if (100 * cost(k) <= pct * cost(tiles) && (!fit || cost(k) < cost(fit))) fit = k;
+    if (fit) return fit;
+  }
+  return tiles;
+}
+
 struct RelPlan {
   RelKind kind;
   int tiles;        // token tiles per frame
@@ -134,27 +172,10 @@ inline RelPlan relevance_plan(const wz_config& c) {
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.rtw = p.tile_tokens <= 64 ? 1 : 2;
   } else {
-    // passes of up to 384 columns; tiles of 16 to 64 tokens, one workgroup to a
-    // CU.  Per 64 channels a workgroup's MFMAs take as long as 16-row tiles x
-    // column tiles, its query reads from L2 as long as four 16-row tiles do:
-    // take the tile count with the least of their sum over a CU's turns, the
-    // smaller count on a tie
+    // passes of up to 384 columns; one workgroup to a CU
     const int passes = (c.Q + 383) / 384;
     p.ntw = (c.Q + 128 * passes - 1) / (128 * passes);
-    const int tr = (c.T + kXcds - 1) / kXcds * kXcds;
-    const int lo = (N + 63) / 64, hi = (N + 15) / 16;
-    long best = -1;
-    for (int k = lo; k <= hi; ++k) {
-      const int rows = ((N + k - 1) / k + 15) / 16 * 16;
-      const long cost = long((long(tr) * k + kCUs - 1) / kCUs) * (rows + 64);
-      if (best < 0 || cost < best) best = cost, p.tiles = k;
-    }
-    // The tiles' channel and column sums are the workspace's largest part: where
-    // they would take the call past the allocation-free scratch (with 20 bytes
-    // a token for scores, ranks and gates, and the alignment of the arrays),
-    // tiles of up to 256 tokens, in stretches of at most 64
-    const size_t rest = size_t(c.T) * (c.Q * 4 + size_t(N) * 20 + 16) + 16 * 256;
-    if (size_t(c.T) * p.tiles * (size_t(c.C) + c.Q) * 4 + rest > kScratchBytes) p.tiles = (N + 255) / 256;
+    p.tiles = wide_tiles(c);
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.sub = (p.tile_tokens + 63) / 64;
     p.mt = ((p.tile_tokens + p.sub - 1) / p.sub + 15) / 16;
@@ -203,9 +224,8 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // split: room for the filter-bank operator rows when the problem uses them
 // (without it the modulator runs its fused form, which keeps them in LDS).
-inline Workspace workspace_layout(const wz_config& c, char* base, bool split = true) {
-  const RelPlan pl = relevance_plan(c);
-  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q, tiles = pl.tiles;
+inline Workspace workspace_carve(const wz_config& c, size_t tiles, char* base, bool split) {
+  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q;
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + off : nullptr; off += align256(bytes); return p; };
@@ -225,6 +245,12 @@ inline Workspace workspace_layout(const wz_config& c, char* base, bool split = t
   w.frows = frows ? reinterpret_cast<uint16_t*>(take(frows)) : nullptr;
   w.bytes = off;
   return w;
+}
+inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split) {
+  return workspace_carve(c, tiles, nullptr, split).bytes;
+}
+inline Workspace workspace_layout(const wz_config& c, char* base, bool split = true) {
+  return workspace_carve(c, relevance_plan(c).tiles, base, split);
 }
 
 // Several videos in one launch: video v = blockIdx.y of every kernel works

@@ -1,0 +1,92 @@
+"""The decomposition of the relevance pass (csrc/wz_internal.h), evaluated on the host: a small program compiled against
+the header prints the plan and the workspace of each shape.  No GPU needed."""
+import os
+import subprocess
+
+import pytest
+
+import libutil
+from paper_2607_23265_amd import wavezip as wz
+from paper_2607_23265_amd.csrc import build
+
+TOK, WG, WIDE = range(3)
+SCRATCH = 32 << 20
+CUS = 256
+
+PROBE = r"""
+#include <cstdio>
+#include "wz_internal.h"
+int main() {
+  wz_config c{};
+  c.levels = 1; c.tau = 0.f; c.lambda_ = 1.5f; c.spatial_levels = 1; c.out_dtype = WZ_F32;
+  int T, H, W, C, Q, dt, basis;
+  long long B;
+  while (scanf("%d %d %d %d %d %d %d %lld", &T, &H, &W, &C, &Q, &dt, &basis, &B) == 8) {
+    c.T = T; c.H = H; c.W = W; c.C = C; c.Q = Q; c.in_dtype = dt; c.spatial_basis = basis; c.B = B;
+    const wz::RelPlan p = wz::relevance_plan(c);
+    printf("%d %d %d %d %d %d %d %zu %zu\n", p.kind, p.tiles, p.tile_tokens, p.mt, p.sub, p.ntw, p.grid,
+           wz::workspace_layout(c, nullptr, true).bytes, wz::workspace_layout(c, nullptr, false).bytes);
+  }
+}
+"""
+FIELDS = ("kind", "tiles", "tile_tokens", "mt", "sub", "ntw", "grid", "bytes", "bytes_fused")
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    libutil.ensure_built()
+    d = tmp_path_factory.mktemp("plan")
+    src, exe = str(d / "plan.hip"), str(d / "plan")
+    with open(src, "w") as f:
+        f.write(PROBE)
+    libdir = os.path.dirname(wz.LIB_PATH)
+    subprocess.run([build.hipcc(), "-O1", "-std=c++17", "--offload-host-only", "-I", build.INCLUDE, "-I", build.HERE,
+                    src, f"-L{libdir}", f"-l:{os.path.basename(wz.LIB_PATH)}", f"-Wl,-rpath,{libdir}", "-o", exe],
+                   check=True, capture_output=True, timeout=300)
+
+    def run(T, H, W, C, Q, dtype=wz.WZ_BF16, basis=wz.WZ_HAAR, B=1):
+        r = subprocess.run([exe], input=f"{T} {H} {W} {C} {Q} {dtype} {basis} {B}\n", capture_output=True, text=True,
+                           check=True, timeout=60)
+        return dict(zip(FIELDS, map(int, r.stdout.split())))
+
+    return run
+
+
+def test_kinds(plan):
+    assert plan(64, 14, 14, 3584, 32)["kind"] == TOK
+    assert plan(64, 14, 14, 3584, 300, wz.WZ_F32)["kind"] == TOK
+    assert plan(256, 27, 27, 1152, 128)["kind"] == WG
+    assert plan(64, 14, 14, 3584, 300)["kind"] == WIDE
+
+
+def wide_cost(T, tiles, sub, mt):
+    """Turns of a CU, times the 16-row tiles and the query reads (as long as four of them) of its stretches."""
+    return -(-(-(-T // 8) * 8 * tiles) // CUS) * sub * (mt + 4)
+
+
+# few frames of many tokens, frames enough for turns; sums past the scratch at the best tiles, or whatever the tiles
+@pytest.mark.parametrize("T,H,W,C,Q", [(4, 64, 64, 32768, 300), (8, 64, 64, 16384, 300), (16, 15, 15, 65536, 130),
+                                       (64, 14, 14, 65536, 129), (260, 14, 14, 16384, 130), (260, 14, 14, 8192, 130),
+                                       (512, 14, 14, 3584, 300), (1040, 14, 14, 1024, 1024), (64, 14, 14, 3584, 300)])
+def test_wide_query_tiles_cost(plan, T, H, W, C, Q):
+    """Sums that pass the allocation-free call's scratch cost a call at most a quarter more than the best tiles, above
+    256 query tokens at most half more."""
+    p, N = plan(T, H, W, C, Q), H * W
+    best = min(wide_cost(T, k, 1, -(-(-(-N // k)) // 16)) for k in range(-(-N // 64), -(-N // 16) + 1))
+    assert p["kind"] == WIDE and wide_cost(T, p["tiles"], p["sub"], p["mt"]) <= (1.25 if Q <= 256 else 1.5) * best
+
+
+# (a slightly dearer count that fits is taken, the finest ones being just past the scratch)
+@pytest.mark.parametrize("T,H,W,C,Q,tiles", [(260, 14, 14, 8192, 130, 2), (260, 14, 14, 8192, 300, 2),
+                                             (256, 15, 15, 8192, 130, 1), (256, 15, 15, 8192, 400, 1),
+                                             (128, 19, 21, 9216, 400, 2), (856, 25, 32, 496, 815, 4)])
+def test_wide_query_tiles_within_the_scratch(plan, T, H, W, C, Q, tiles):
+    p = plan(T, H, W, C, Q)
+    assert p["kind"] == WIDE and p["bytes"] <= SCRATCH
+    assert p["tiles"] == tiles and p["sub"] > 1 and p["mt"] <= 4 and p["sub"] * 16 * p["mt"] >= p["tile_tokens"]
+
+
+def test_wide_query_operator_rows_stay_in_the_scratch(plan):
+    """A filter-bank call whose operator rows fitted the scratch beside coarser tiles' sums keeps them there."""
+    p = plan(418, 31, 29, 24, 620, basis=wz.WZ_DB4, B=4842)
+    assert p["kind"] == WIDE and p["bytes"] <= SCRATCH
