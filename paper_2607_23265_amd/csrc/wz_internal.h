@@ -83,20 +83,24 @@ inline RelKind relevance_kind(const wz_config& c) {
   if (c.in_dtype != WZ_BF16 || c.Q <= 32) return kRelTok;  // (fp32: passes of 32 columns above 64 query tokens)
   if (c.Q > 64) return c.Q <= 128 ? kRelWg : kRelWide;
   // 33 to 64 query tokens: channel stripes leave one workgroup to a CU, whose
-  // turns do not overlap (about 4 us, and 3 us for each eight 64-channel
-  // chunks); the shared tiles leave two, with a barrier a chunk (0.9 us; tiles
-  // of more than 64 tokens 1.45 us).  At Q = 48, channel stripes against shared
-  // tiles: T = 512, 14x14, C = 768 74.2 / 44.4 us; T = 256, 27x27, C = 1152
-  // 163.1 / 121.9; T = 200, 14x14, C = 2560 67.9 / 58.7; T = 150, 20x20, C =
-  // 1536 68.7 / 67.5; T = 512, 8x8, C = 3584 54.7 / 62.4; T = 110, 12x12, C =
-  // 4096 44.3 / 61.5.  Finer tiles than the stripes' would also take more
-  // workspace.
+  // turns do not overlap; the shared tiles leave two, with a barrier a chunk.
+  // The shared tiles where they take fewer turns and less time, both in ns
+  // from 300 shapes with H, W up to 64, C up to 10240 (median error 4 %; the
+  // choice is within 4 % of the better one on each, 1 % slower on average): a
+  // turn of the stripes by its tile's rows in eighths, of the shared tiles in
+  // sixteenths.  At Q = 48, channel stripes against shared tiles: T = 512,
+  // 14x14, C = 768 74.2 / 44.4 us; T = 256, 27x27, C = 1152 163.1 / 121.9; T =
+  // 200, 14x14, C = 2560 67.9 / 58.7; T = 512, 8x8, C = 3584 54.7 / 62.4; T =
+  // 74, 14x14, C = 3168 40.4 / 49.8; T = 289, 10x2, C = 3672 36.6 / 53.0.  Finer
+  // tiles than the stripes' would also take more workspace.  (The videos of a
+  // batch do not count: each has the bits of its single call.)
   const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, chunks = (c.C + 63) / 64;
   const int kt = rel_tiles(c, 64, kCUs, 64), kw = rel_tiles(c, 128, 2 * kCUs, 64);
   const long turns_t = (long(tr) * kt + kCUs - 1) / kCUs, turns_w = (long(tr) * kw + 2 * kCUs - 1) / (2 * kCUs);
-  const long tok = turns_t * (80 + 60 * ((chunks + 7) / 8));                           // in 0.05 us
-  const long wg = turns_w * chunks * ((N + kw - 1) / kw <= 64 ? 18 : 29) + 60;
-  return kw <= kt && wg < tok ? kRelWg : kRelTok;
+  const int rows_t = ((N + kt - 1) / kt + 7) / 8 * 8, rows_w = ((N + kw - 1) / kw + 15) / 16 * 16;
+  const long tok = 4300 + turns_t * (4800 + chunks * (74 + 16 * rows_t / 3));
+  const long wg = 5400 + turns_w * (4500 + chunks * (540 + (rows_w <= 64 ? 5 * rows_w : 37 * rows_w / 5)));
+  return kw <= kt && turns_w < turns_t && 100 * wg < 96 * tok ? kRelWg : kRelTok;
 }
 
 // Workspace bytes at `tiles` token tiles a frame (see workspace_layout).

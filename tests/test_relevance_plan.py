@@ -59,6 +59,23 @@ def test_kinds(plan):
     assert plan(64, 14, 14, 3584, 300)["kind"] == WIDE
 
 
+# wz_relevance in us, channel stripes / shared tiles
+@pytest.mark.parametrize("T,H,W,C,Q,kind", [
+    (512, 14, 14, 768, 48, WG), (256, 27, 27, 1152, 48, WG), (96, 27, 27, 1152, 48, WG), (200, 14, 14, 2560, 48, WG),
+    (512, 8, 8, 3584, 48, TOK), (110, 12, 12, 4096, 48, TOK), (128, 13, 13, 3584, 64, TOK),
+    (74, 14, 14, 3168, 53, TOK),   # 40.4 / 49.8
+    (33, 27, 24, 3264, 56, TOK),   # 44.1 / 52.4
+    (135, 8, 13, 2344, 37, TOK),   # 34.8 / 39.0
+    (289, 10, 2, 3672, 35, TOK),   # 36.6 / 53.0
+    (68, 16, 16, 3664, 44, TOK),   # 44.8 / 56.4
+    (1917, 2, 2, 2536, 49, TOK),   # 83.2 / 125.2
+    (1, 9, 7, 200, 46, TOK),       # 7.8 / 9.2
+])
+def test_middle_query_kind(plan, T, H, W, C, Q, kind):
+    """33 to 64 query tokens: the kernel that measured faster."""
+    assert plan(T, H, W, C, Q)["kind"] == kind
+
+
 def wide_cost(T, tiles, sub, mt):
     """Turns of a CU, times the 16-row tiles and the query reads (as long as four of them) of its stretches."""
     return -(-(-(-T // 8) * 8 * tiles) // CUS) * sub * (mt + 4)
