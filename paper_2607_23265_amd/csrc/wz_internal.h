@@ -50,13 +50,13 @@ constexpr size_t kScratchBytes = size_t(32) << 20;
 
 // Streaming kernels of the relevance pass, chosen by shape:
 //   kRelTok  fp32; bf16, Q <= 64: token tiles, each wave a channel stripe with
-//            its own LDS-transposed MFMA (fp32 above 64 query tokens: passes
-//            of 32 columns per tile);
+//            its own LDS-transposed MFMA (above 64 query tokens, fp32 or where
+//            wide_takes_passes says: passes of 32 columns per tile);
 //   kRelWg   bf16, 64 < Q <= 128 (and 32 < Q <= 64, see relevance_kind): the
 //            workgroup's waves share each channel chunk of the tile and the
 //            query in LDS, each wave some 16-row tiles against every column;
-//   kRelWide bf16, Q > 128: the waves split the query's columns and share
-//            each chunk of the tile in LDS.
+//   kRelWide bf16, Q > 128 (but see wide_takes_passes): the waves split the
+//            query's columns and share each chunk of the tile in LDS.
 enum RelKind { kRelTok = 0, kRelWg = 1, kRelWide = 2 };
 
 // Token tiles per frame of at most `cap` tokens for `slots` workgroups running
@@ -79,9 +79,79 @@ inline int rel_tiles(const wz_config& c, int cap, int slots, int qrows) {
   return tiles;
 }
 
+// Workspace bytes at `tiles` token tiles a frame (see workspace_layout).
+inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split);
+
+// Token tiles per frame of kRelWide: of 16 to 64 tokens, or of up to 256 in
+// stretches of at most 64.  Per 64 channels a stretch's MFMAs take as long as
+// 16-row tiles x column tiles, its query reads from L2 as long as four 16-row
+// tiles do: their sum over a CU's turns is the cost of a count.
+inline long wide_cost(const wz_config& c, int tiles) {
+  const int tr = (c.T + kXcds - 1) / kXcds * kXcds, tt = (c.H * c.W + tiles - 1) / tiles, sub = (tt + 63) / 64;
+  const int rows = ((tt + sub - 1) / sub + 15) / 16 * 16;
+  return long((long(tr) * tiles + kCUs - 1) / kCUs) * sub * (rows + 64);
+}
+// the cheapest count of tiles of at most 64 tokens, the smaller on a tie
+inline int wide_best_tiles(const wz_config& c) {
+  const int N = c.H * c.W;
+  int tiles = (N + 63) / 64;
+  for (int k = tiles + 1; k <= (N + 15) / 16; ++k)
+    if (wide_cost(c, k) < wide_cost(c, tiles)) tiles = k;
+  return tiles;
+}
+inline int wide_tiles(const wz_config& c) {
+  const int N = c.H * c.W, tiles = wide_best_tiles(c);
+  // The tiles' channel and column sums are the workspace's largest part.  Where
+  // they do not fit the allocation-free call's scratch, the cheapest count that
+  // does (with the filter-bank operator rows, else without), if its cost is not
+  // too far up; otherwise the caller's workspace holds the finer tiles.  The
+  // line: a quarter more up to 256 query tokens (wz_relevance, T = 260, 14x14,
+  // C = 8192, Q = 130: passes of 32 columns 715 us, tiles of 256 tokens, at 1.6
+  // times the cost, 809, of 98 tokens, at 1.2 times, 610; T = 4, 64x64, C =
+  // 32768, Q = 300: 2305 us in tiles of 256 tokens on a quarter of the chip, of
+  // 128 tokens 1346); half more above, where the scratch has always held tiles
+  // of 256 tokens up to C = 1024 (at most 1.43 times the cost there).
+  const long pct = c.Q <= 256 ? 125 : 150;
+  for (const bool split : {true, false}) {
+    if (workspace_bytes_at(c, tiles, split) <= kScratchBytes) break;
+    int fit = 0;
+    for (int k = (N + 255) / 256; k <= (N + 15) / 16 && workspace_bytes_at(c, k, split) <= kScratchBytes; ++k)
+      if (100 * wide_cost(c, k) <= pct * wide_cost(c, tiles) && (!fit || wide_cost(c, k) < wide_cost(c, fit))) fit = k;
+    if (fit) return fit;
+  }
+  return tiles;
+}
+
+// Whether 129 to 256 bf16 query tokens take passes of 32 columns (kRelTok)
+// instead of kRelWide.  Up to 4096 channels they do not: kRelWide is never
+// slower than passes were there, and its sums are nearer to 64 bits.  Above, a
+// few tokens a CU leave its eight waves waiting for a long query in step with
+// one another, where a wave of the passes waits for its own chunks alone.  Both
+// times in ns, from 350 shapes up to T = 2048, 64x64, C = 65536 (median error 5
+// %; the choice is within 6 % of the better one on all but one): a turn's
+// latency by passes or chunks and rows (tiles of at most 32 tokens, larger ones
+// never gain), or the bytes that every workgroup reads of X and the query.
+// Passes against kRelWide, wz_relevance in us: T = 1, one token, C = 32768, Q =
+// 129 232 / 302; T = 434, one token, C = 16384, Q = 160 255 / 310; T = 16,
+// 15x15, C = 16384, Q = 129 161 / 175; T = 3, 27x27, C = 16384, Q = 200 250 /
+// 211; T = 260, 14x14, C = 8192, Q = 130 715 / 610.
+inline bool wide_takes_passes(const wz_config& c) {
+  if (c.Q > 256 || c.C <= 4096) return false;
+  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, chunks = (c.C + 63) / 64, np = (c.Q + 31) / 32;
+  const int kt = rel_tiles(c, 64, kCUs, 32), kw = wide_best_tiles(c);
+  const long turns_t = (long(tr) * kt + kCUs - 1) / kCUs, turns_w = (long(tr) * kw + kCUs - 1) / kCUs;
+  const int rows_t = ((N + kt - 1) / kt + 7) / 8 * 8, mt = ((N + kw - 1) / kw + 15) / 16;
+  const long x = long(c.T) * N * c.C * 2, q = long(c.Q) * c.C * 2;
+  const long passes = std::max(3100 + turns_t * (3850 + np * (1650 + chunks * (23 + 18 * rows_t / 5))),
+                               (np * x * 147 + c.T * kt * q * 73) / 1000000);
+  const long wide = std::max(4700 + turns_w * (3400 + (chunks + 3) / 4 * (2300 + 300 * mt)),
+                             (x * 200 + c.T * kw * q * 123) / 1000000);
+  return rows_t <= 32 && 100 * passes < 95 * wide;
+}
+
 inline RelKind relevance_kind(const wz_config& c) {
-  if (c.in_dtype != WZ_BF16 || c.Q <= 32) return kRelTok;  // (fp32: passes of 32 columns above 64 query tokens)
-  if (c.Q > 64) return c.Q <= 128 ? kRelWg : kRelWide;
+  if (c.in_dtype != WZ_BF16 || c.Q <= 32) return kRelTok;
+  if (c.Q > 64) return c.Q <= 128 ? kRelWg : wide_takes_passes(c) ? kRelTok : kRelWide;
   // 33 to 64 query tokens: channel stripes leave one workgroup to a CU, whose
   // turns do not overlap; the shared tiles leave two, with a barrier a chunk.
   // The shared tiles where they take fewer turns and less time, both in ns
@@ -101,44 +171,6 @@ inline RelKind relevance_kind(const wz_config& c) {
   const long tok = 4300 + turns_t * (4800 + chunks * (74 + 16 * rows_t / 3));
   const long wg = 5400 + turns_w * (4500 + chunks * (540 + (rows_w <= 64 ? 5 * rows_w : 37 * rows_w / 5)));
   return kw <= kt && turns_w < turns_t && 100 * wg < 96 * tok ? kRelWg : kRelTok;
-}
-
-// Workspace bytes at `tiles` token tiles a frame (see workspace_layout).
-inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split);
-
-// Token tiles per frame of kRelWide: of 16 to 64 tokens, or of up to 256 in
-// stretches of at most 64.  Per 64 channels a stretch's MFMAs take as long as
-// 16-row tiles x column tiles, its query reads from L2 as long as four 16-row
-// tiles do: take the count with the least of their sum over a CU's turns, the
-// smaller count on a tie.
-inline int wide_tiles(const wz_config& c) {
-  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, hi = (N + 15) / 16;
-  auto cost = [&](int k) {
-    const int tt = (N + k - 1) / k, sub = (tt + 63) / 64, rows = ((tt + sub - 1) / sub + 15) / 16 * 16;
-    return long((long(tr) * k + kCUs - 1) / kCUs) * sub * (rows + 64);
-  };
-  int tiles = (N + 63) / 64;
-  for (int k = tiles + 1; k <= hi; ++k)
-    if (cost(k) < cost(tiles)) tiles = k;
-  // The tiles' channel and column sums are the workspace's largest part.  Where
-  // they do not fit the allocation-free call's scratch, the cheapest count that
-  // does (with the filter-bank operator rows, else without), if its cost is not
-  // too far up; otherwise the caller's workspace holds the finer tiles.  The
-  // line: a quarter more up to 256 query tokens (wz_relevance, T = 260, 14x14,
-  // C = 8192, Q = 130: passes of 32 columns 715 us, tiles of 256 tokens, at 1.6
-  // times the cost, 809, of 98 tokens, at 1.2 times, 610; T = 4, 64x64, C =
-  // 32768, Q = 300: 2305 us in tiles of 256 tokens on a quarter of the chip, of
-  // 128 tokens 1346); half more above, where the scratch has always held tiles
-  // of 256 tokens up to C = 1024 (at most 1.43 times the cost there).
-  const long pct = c.Q <= 256 ? 125 : 150;
-  for (const bool split : {true, false}) {
-    if (workspace_bytes_at(c, tiles, split) <= kScratchBytes) break;
-    int fit = 0;
-    for (int k = (N + 255) / 256; k <= hi && workspace_bytes_at(c, k, split) <= kScratchBytes; ++k)
-      if (100 * cost(k) <= pct * cost(tiles) && (!fit || cost(k) < cost(fit))) fit = k;
-    if (fit) return fit;
-  }
-  return tiles;
 }
 
 struct RelPlan {

@@ -8,8 +8,8 @@
 // in a fixed order and forms r_t and delta_t.
 //
 // Three decompositions, each with every channel in a workgroup:
-//  * token tiles (fp32 inputs; bf16, Q <= 64): a workgroup owns up to 64 tokens
-//    of a frame, its waves split the channels;
+//  * token tiles (fp32 inputs; bf16, Q <= 64 and some of 128 < Q <= 256): a
+//    workgroup owns up to 64 tokens of a frame, its waves split the channels;
 //  * shared token tiles (bf16, 64 < Q <= 128, and 32 < Q <= 64 where a CU would
 //    take turns of the former): the waves share each chunk of
 //    the tile and of the query in LDS and split S;
@@ -103,7 +103,7 @@ __device__ __forceinline__ void mfma_units(const u32x4 (&A)[MT], const u32x4 (&B
 }
 
 // ---------------------------------------------------------------------------
-// Token-tiled path (fp32 inputs; bf16, Q <= 64)
+// Token-tiled path (fp32 inputs; bf16, Q <= 64 and some of 128 < Q <= 256)
 // ---------------------------------------------------------------------------
 // (Described for bf16 inputs; an fp32 chunk is 32 channels, the same bytes,
 // and its S runs on v_mfma_f32_16x16x4_f32.  Bound for fp32: HBM up to about
@@ -1095,8 +1095,9 @@ void launch_tok(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipSt
   if (va.v[0].groups > 1) {
     launch_tok_mode<In, NTG, IPC, kTokGroups>(pl, va, V, s);
   } else if (va.v[0].Q > 16 * NTG) {
-    // fp32 inputs; the plan takes two query tiles for passes (checked by the caller)
-    if constexpr (NTG == 2 && sizeof(In) == 4) launch_tok_mode<In, NTG, IPC, kTokPasses>(pl, va, V, s);
+    // the plan takes two query tiles for passes, with bf16 inputs tiles of at
+    // most 32 tokens (checked by the caller)
+    if constexpr (NTG == 2 && (sizeof(In) == 4 || IPC <= 4)) launch_tok_mode<In, NTG, IPC, kTokPasses>(pl, va, V, s);
   } else {
     launch_tok_mode<In, NTG, IPC, kTokOne>(pl, va, V, s);
   }
@@ -1153,7 +1154,8 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
   }
   if (pl.kind == kRelTok) {
     // columns beyond the query tiles are served by passes of two tiles only
-    if (va.v[0].Q > 16 * pl.ntg && (pl.ntg != 2 || va.v[0].groups > 1 || c.in_dtype == WZ_BF16)) return hipErrorInvalidValue;
+    if (va.v[0].Q > 16 * pl.ntg && (pl.ntg != 2 || va.v[0].groups > 1 || (c.in_dtype == WZ_BF16 && pl.ipc > 4)))
+      return hipErrorInvalidValue;
     if (c.in_dtype == WZ_BF16) launch_tok_shape<uint16_t>(pl, va, V, s);
     else launch_tok_shape<float>(pl, va, V, s);
   } else if (pl.kind == kRelWg) {

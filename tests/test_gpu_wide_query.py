@@ -48,6 +48,14 @@ def test_wide_query(T, H, W, C, Q):
     assert G.within(d.cpu().numpy(), out["delta"], G.TOL_F32_IN, "delta")
 
 
+# passes of 32 columns over tiles of at most 32 tokens (long rows, up to 192 query tokens): one token, 16-row MFMA tiles
+# whole, ragged and two; channel sums in LDS (C <= 8192) and stored by chunk; five and six passes, ragged last ones
+@pytest.mark.parametrize("T,H,W,C,Q", [(3, 1, 1, 4104, 129), (2, 4, 4, 8192, 160), (434, 1, 1, 4104, 161),
+                                       (3, 7, 9, 16392, 192), (2, 7, 8, 8256, 129), (128, 6, 6, 8192, 130)])
+def test_passes_over_long_rows(T, H, W, C, Q):
+    test_wide_query(T, H, W, C, Q)
+
+
 def test_stretches_within_the_scratch():
     """Tiles whose sums would not fit the allocation-free call's scratch are taken in stretches: the call is accepted,
     with the scores and relevances of the definition."""

@@ -76,13 +76,29 @@ def test_middle_query_kind(plan, T, H, W, C, Q, kind):
     assert plan(T, H, W, C, Q)["kind"] == kind
 
 
+# wz_relevance in us, passes of 32 columns / one pass; up to 4096 channels the one pass throughout
+@pytest.mark.parametrize("T,H,W,C,Q,kind", [
+    (1, 1, 1, 32768, 129, TOK),      # 232 / 302
+    (434, 1, 1, 16384, 160, TOK),    # 255 / 310
+    (1360, 1, 6, 36656, 130, TOK),   # 1758 / 2099
+    (16, 15, 15, 16384, 129, TOK),   # 161 / 175
+    (260, 14, 14, 8192, 130, WIDE),  # 715 / 610
+    (3, 27, 27, 16384, 200, WIDE),   # 250 / 211
+    (1, 1, 1, 4096, 129, WIDE), (64, 7, 7, 3584, 129, WIDE), (2, 4, 4, 16384, 256, WIDE),
+])
+def test_passes_or_one_pass(plan, T, H, W, C, Q, kind):
+    """129 to 256 query tokens: the kernel that measured faster."""
+    p = plan(T, H, W, C, Q)
+    assert p["kind"] == kind and (kind == WIDE or p["tile_tokens"] <= 32)
+
+
 def wide_cost(T, tiles, sub, mt):
     """Turns of a CU, times the 16-row tiles and the query reads (as long as four of them) of its stretches."""
     return -(-(-(-T // 8) * 8 * tiles) // CUS) * sub * (mt + 4)
 
 
 # few frames of many tokens, frames enough for turns; sums past the scratch at the best tiles, or whatever the tiles
-@pytest.mark.parametrize("T,H,W,C,Q", [(4, 64, 64, 32768, 300), (8, 64, 64, 16384, 300), (16, 15, 15, 65536, 130),
+@pytest.mark.parametrize("T,H,W,C,Q", [(4, 64, 64, 32768, 300), (8, 64, 64, 16384, 300), (16, 15, 15, 65536, 230),
                                        (64, 14, 14, 65536, 129), (260, 14, 14, 16384, 130), (260, 14, 14, 8192, 130),
                                        (512, 14, 14, 3584, 300), (1040, 14, 14, 1024, 1024), (64, 14, 14, 3584, 300)])
 def test_wide_query_tiles_cost(plan, T, H, W, C, Q):
