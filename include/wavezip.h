@@ -151,8 +151,11 @@ wz_status wz_relevance(const wz_config* cfg, const void* X, const void* query,
 
 /* The pass over X that stage 1 starts with -- the one kernel of the whole
  * pass that reads the frames -- on its own.  It writes the per-token scores
- * a_{t,n} to tok_score [T*H*W] and leaves in ws the per-work-unit partial
- * sums that wz_relevance's per-frame step completes r_t and delta_t from.  It
+ * a_{t,n} to tok_score [T*H*W] (unless the grid has slices of channels, which
+ * only calls with more than 256 bf16 query tokens and more than 8192 channels
+ * have), and leaves in ws the per-work-unit partial sums that wz_relevance's
+ * per-frame step completes r_t, delta_t (and, with channel slices, a_{t,n})
+ * from.  It
  * lets a caller run or time the pass alone; nothing else reads what it
  * leaves in ws.  Same arguments and checks as wz_relevance.  One kernel
  * launch.                                                                     */

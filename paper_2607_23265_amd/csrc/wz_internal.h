@@ -39,11 +39,15 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // ---------------------------------------------------------------------------
 // Decomposition of the relevance pass (shapes and limits; the kernels'
-// comments give the details): token tiles of a frame, each with every channel.
+// comments give the details): token tiles of a frame, each with every channel
+// (kRelSlices: also slices of channels).
 // ---------------------------------------------------------------------------
 constexpr int kXcds = 8;          // MI355X: workgroups are dealt to the 8 XCDs round robin
 constexpr int kCUs = 256;
 constexpr int kTokMax = 4096;     // validated bound on tokens per frame
+constexpr int kMaxWaves = 16;     // kRelSlices: 16-row MFMA tiles per token tile
+constexpr int kTilesPerWave = 2;  // kRelSlices: 16-row MFMA tiles per wave
+constexpr int kSliceSteps = 32;   // kRelSlices: 32-channel steps per slice at most (the query slice sits in LDS)
 
 // Scratch of the allocation-free call.
 constexpr size_t kScratchBytes = size_t(32) << 20;
@@ -55,9 +59,15 @@ constexpr size_t kScratchBytes = size_t(32) << 20;
 //   kRelWg   bf16, 64 < Q <= 128 (and 32 < Q <= 64, see relevance_kind): the
 //            workgroup's waves share each channel chunk of the tile and the
 //            query in LDS, each wave some 16-row tiles against every column;
-//   kRelWide bf16, Q > 128 (but see wide_takes_passes): the waves split the
-//            query's columns and share each chunk of the tile in LDS.
-enum RelKind { kRelTok = 0, kRelWg = 1, kRelWide = 2 };
+//   kRelWide bf16, Q > 128 (but see wide_takes_passes, wide_takes_slices): the
+//            waves split the query's columns and share each chunk of the tile
+//            in LDS;
+//   kRelSlices bf16, Q > 256 where wide_takes_slices says: tiles of up to 256
+//            tokens, slices of channels.
+enum RelKind { kRelTok = 0, kRelWg = 1, kRelWide = 2, kRelSlices = 3 };
+
+// Query columns of the slices' partial scores, padded for 16-byte rows.
+inline int qpad(int Q) { return (Q + 3) & ~3; }
 
 // Token tiles per frame of at most `cap` tokens for `slots` workgroups running
 // at once: the count (tiles of 16 tokens and up) with the fewest rows of X and
@@ -79,7 +89,7 @@ inline int rel_tiles(const wz_config& c, int cap, int slots, int qrows) {
   return tiles;
 }
 
-// Workspace bytes at `tiles` token tiles a frame (see workspace_layout).
+// Workspace bytes at `tiles` token tiles a frame, one slice (see workspace_layout).
 inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split);
 
 // Token tiles per frame of kRelWide: of 16 to 64 tokens, or of up to 256 in
@@ -122,36 +132,88 @@ inline int wide_tiles(const wz_config& c) {
   return tiles;
 }
 
+// Time of kRelWide's pass in ns, from 1050 shapes over the whole accepted range
+// (median error 6 %): a turn's latency by passes, chunks, column and row tiles,
+// or the bytes that every workgroup reads of X and the query.
+inline int wide_passes(const wz_config& c) { return (c.Q + 383) / 384; }  // of up to 384 columns
+inline int wide_ntw(const wz_config& c) { return (c.Q + 128 * wide_passes(c) - 1) / (128 * wide_passes(c)); }
+inline long wide_ns(const wz_config& c) {
+  const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, kw = wide_best_tiles(c), ntw = wide_ntw(c);
+  const int mt = ((N + kw - 1) / kw + 15) / 16;
+  const long turns = (long(tr) * kw + kCUs - 1) / kCUs;
+  return 5000 + std::max(turns * wide_passes(c) * (2800 + (c.C + 255) / 256 * (700 + 900 * ntw + 180 * mt * ntw)),
+                         (long(c.T) * N * c.C * 200 + long(c.T) * kw * c.Q * c.C * 260) / 1000000);
+}
+
 // Whether 129 to 256 bf16 query tokens take passes of 32 columns (kRelTok)
 // instead of kRelWide.  Up to 4096 channels they do not: kRelWide is never
 // slower than passes were there, and its sums are nearer to 64 bits.  Above, a
 // few tokens a CU leave its eight waves waiting for a long query in step with
-// one another, where a wave of the passes waits for its own chunks alone.  Both
-// times in ns, from 350 shapes up to T = 2048, 64x64, C = 65536 (median error 5
-// %; the choice is within 6 % of the better one on all but one): a turn's
-// latency by passes or chunks and rows (tiles of at most 32 tokens, larger ones
-// never gain), or the bytes that every workgroup reads of X and the query.
-// Passes against kRelWide, wz_relevance in us: T = 1, one token, C = 32768, Q =
-// 129 232 / 302; T = 434, one token, C = 16384, Q = 160 255 / 310; T = 16,
-// 15x15, C = 16384, Q = 129 161 / 175; T = 3, 27x27, C = 16384, Q = 200 250 /
-// 211; T = 260, 14x14, C = 8192, Q = 130 715 / 610.
+// one another, where a wave of the passes waits for its own chunks alone (in
+// tiles of at most 32 tokens; larger ones never gain).  The passes' time by
+// passes, chunks and rows, or the bytes read (600 shapes, median error 5 %; the
+// choice is within 8 % of the better one on all but one).  Passes against
+// kRelWide, wz_relevance in us: T = 1, one token, C = 32768, Q = 129 232 / 302;
+// T = 434, one token, C = 16384, Q = 160 255 / 310; T = 16, 15x15, C = 16384, Q
+// = 129 161 / 175; T = 3, 27x27, C = 16384, Q = 200 250 / 211; T = 260, 14x14, C
+// = 8192, Q = 130 715 / 610.
 inline bool wide_takes_passes(const wz_config& c) {
   if (c.Q > 256 || c.C <= 4096) return false;
   const int N = c.H * c.W, tr = (c.T + kXcds - 1) / kXcds * kXcds, chunks = (c.C + 63) / 64, np = (c.Q + 31) / 32;
-  const int kt = rel_tiles(c, 64, kCUs, 32), kw = wide_best_tiles(c);
-  const long turns_t = (long(tr) * kt + kCUs - 1) / kCUs, turns_w = (long(tr) * kw + kCUs - 1) / kCUs;
-  const int rows_t = ((N + kt - 1) / kt + 7) / 8 * 8, mt = ((N + kw - 1) / kw + 15) / 16;
-  const long x = long(c.T) * N * c.C * 2, q = long(c.Q) * c.C * 2;
-  const long passes = std::max(3100 + turns_t * (3850 + np * (1650 + chunks * (23 + 18 * rows_t / 5))),
-                               (np * x * 147 + c.T * kt * q * 73) / 1000000);
-  const long wide = std::max(4700 + turns_w * (3400 + (chunks + 3) / 4 * (2300 + 300 * mt)),
-                             (x * 200 + c.T * kw * q * 123) / 1000000);
-  return rows_t <= 32 && 100 * passes < 95 * wide;
+  const int kt = rel_tiles(c, 64, kCUs, 32), rows = ((N + kt - 1) / kt + 7) / 8 * 8;
+  const long turns = (long(tr) * kt + kCUs - 1) / kCUs;
+  const long passes = std::max(3100 + turns * (3850 + np * (1650 + chunks * (23 + 18 * rows / 5))),
+                               (long(c.T) * N * c.C * np * 294 + long(c.T) * kt * c.Q * c.C * 146) / 1000000);
+  return rows <= 32 && 100 * passes < 95 * wide_ns(c);
+}
+
+// kRelSlices: tiles of up to 256 tokens; slices of at most kSliceSteps steps,
+// more while the grid is short of one workgroup per CU, keeping slices of at
+// least 8 channel steps and per-slice partial scores (4*Q bytes a token) under a
+// quarter of X (2*C).
+struct SlicePlan {
+  int tiles, steps, slices;  // token tiles per frame; 32-channel steps per slice; slices
+};
+inline SlicePlan slice_plan(const wz_config& c) {
+  const int N = c.H * c.W, cap = 16 * kMaxWaves, ksteps = (c.C + 31) / 32;
+  SlicePlan p;
+  p.tiles = (N + cap - 1) / cap;
+  const int smin = (ksteps + kSliceSteps - 1) / kSliceSteps;
+  const int smax = std::max(smin, std::min(ksteps / 8, c.C / (8 * c.Q)));
+  int S = smin;
+  while (S < smax && (long long)c.T * p.tiles * S < kCUs) ++S;
+  p.steps = (ksteps + S - 1) / S;
+  p.slices = (ksteps + p.steps - 1) / p.steps;
+  return p;
+}
+// Whether more than 256 bf16 query tokens take channel slices instead of
+// kRelWide (frames of 49 tokens and up: at least two waves a workgroup).  Above
+// 8192 channels a few frames leave kRelWide on a few CUs, each streaming the whole
+// query; below 128 its fixed cost a tile counts; between, kRelWide is as fast or
+// faster (8 % slower at the most seen).  The slices' time by turns, passes of 32
+// columns, steps and rows, or the bytes read, and the per-frame kernel's reads of
+// the partial scores (1300 shapes, median error 6 %; long rows take them where
+// within a tenth, so that a call is at most 14 % slower than with slices, on all
+// but two 8 %, and at most 28 % slower than with kRelWide).  Slices against it,
+// wz_relevance in us: T = 3, 33x2, C = 64408, Q = 816 1280 / 3117; T = 8, 10x12, C
+// = 32768, Q = 300 298 / 439; T = 705, 13x57, C = 56, Q = 817 653 / 795; T = 8,
+// 14x14, C = 16384, Q = 1024 847 / 673; T = 64, 7x7, C = 16384, Q = 300 459 / 236.
+inline bool wide_takes_slices(const wz_config& c) {
+  const int N = c.H * c.W;
+  if (c.Q <= 256 || N < 49 || (c.C >= 128 && c.C <= 8192)) return false;
+  const SlicePlan p = slice_plan(c);
+  const int tr = (c.T + kXcds - 1) / kXcds * kXcds, mt = ((N + p.tiles - 1) / p.tiles + 15) / 16;
+  const long turns = (long(tr) * p.tiles * p.slices + kCUs - 1) / kCUs, part = long(N) * p.slices * c.Q * 4;
+  const long pass = std::max(turns * ((c.Q + 31) / 32) * (2300 + p.steps * (128 + 10 * mt)),
+                             (long(c.T) * N * c.C * 390 + long(c.T) * p.tiles * c.Q * c.C * 216) / 1000000);
+  const long frame = p.slices > 1 ? 7000 + (c.T * part * 1030 + part * 33000) / 1000000 : 0;
+  return 100 * (5800 + pass + frame) < (c.C > 8192 ? 110 : 97) * wide_ns(c);
 }
 
 inline RelKind relevance_kind(const wz_config& c) {
   if (c.in_dtype != WZ_BF16 || c.Q <= 32) return kRelTok;
-  if (c.Q > 64) return c.Q <= 128 ? kRelWg : wide_takes_passes(c) ? kRelTok : kRelWide;
+  if (c.Q > 64)
+    return c.Q <= 128 ? kRelWg : wide_takes_passes(c) ? kRelTok : wide_takes_slices(c) ? kRelSlices : kRelWide;
   // 33 to 64 query tokens: channel stripes leave one workgroup to a CU, whose
   // turns do not overlap; the shared tiles leave two, with a barrier a chunk.
   // The shared tiles where they take fewer turns and less time, both in ns
@@ -177,10 +239,12 @@ struct RelPlan {
   RelKind kind;
   int tiles;        // token tiles per frame
   int tile_tokens;  // tokens per tile (the last tile of a frame may be shorter)
-  int mt;           // kRelWide: 16-row MFMA tiles per stretch
+  int mt;           // kRelWide, kRelSlices: 16-row MFMA tiles per stretch or tile
   int sub;          // kRelWide: stretches of a token tile
   int ntw;          // kRelWide: 16-column tiles per wave
-  int grid;         // workgroups: frames rounded up to a multiple of kXcds, x tiles
+  int slices;       // channel slices (1 but for kRelSlices)
+  int kc;           // kRelSlices: channels per slice
+  int grid;         // workgroups: frames rounded up to a multiple of kXcds, x tiles x slices
   int ipc;          // kRelTok: row load instructions per chunk (tile rows / 8)
   int ntg;          // kRelTok, kRelWg: 16-column query tiles
   int rtw;          // kRelWg: 16-row tiles per wave (tiles of up to 64 * rtw tokens)
@@ -190,6 +254,7 @@ inline RelPlan relevance_plan(const wz_config& c) {
   const int N = c.H * c.W;
   RelPlan p{};
   p.kind = relevance_kind(c);
+  p.slices = 1;
   if (p.kind == kRelTok) {
     // tiles of 16 to 64 tokens with every channel.  A workgroup fills a CU's
     // LDS, so a CU runs (workgroups / CUs rounded up) of them one after
@@ -207,16 +272,22 @@ inline RelPlan relevance_plan(const wz_config& c) {
     p.tiles = rel_tiles(c, 128, 2 * kCUs, 16 * p.ntg);
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.rtw = p.tile_tokens <= 64 ? 1 : 2;
+  } else if (p.kind == kRelSlices) {
+    const SlicePlan sp = slice_plan(c);
+    p.tiles = sp.tiles;
+    p.tile_tokens = (N + p.tiles - 1) / p.tiles;
+    p.mt = (p.tile_tokens + 15) / 16;
+    p.slices = sp.slices;
+    p.kc = sp.steps * 32;
   } else {
-    // passes of up to 384 columns; one workgroup to a CU
-    const int passes = (c.Q + 383) / 384;
-    p.ntw = (c.Q + 128 * passes - 1) / (128 * passes);
+    // one workgroup to a CU
+    p.ntw = wide_ntw(c);
     p.tiles = wide_tiles(c);
     p.tile_tokens = (N + p.tiles - 1) / p.tiles;
     p.sub = (p.tile_tokens + 63) / 64;
     p.mt = ((p.tile_tokens + p.sub - 1) / p.sub + 15) / 16;
   }
-  p.grid = (c.T + kXcds - 1) / kXcds * kXcds * p.tiles;
+  p.grid = (c.T + kXcds - 1) / kXcds * kXcds * p.tiles * p.slices;
   return p;
 }
 
@@ -226,6 +297,14 @@ __device__ __forceinline__ void unit_of_block(int b, int tiles, int& t, int& til
   const int xcd = b % kXcds, slot = b / kXcds;
   t = (slot / tiles) * kXcds + xcd;
   tile = slot % tiles;
+}
+
+// The same with the slices of each tile next to one another.
+__device__ __forceinline__ void slice_of_block(int b, int tiles, int slices, int& t, int& tile, int& slice) {
+  int u;
+  unit_of_block(b, tiles * slices, t, u);
+  tile = u / slices;
+  slice = u % slices;
 }
 
 constexpr int kMaxFrames = 2048;
@@ -240,8 +319,10 @@ constexpr int kFusedTMax = 256;
 size_t filter_rows_bytes(const wz_config& c);
 
 struct Workspace {
-  float* qg_part;      // [T][Q]                  |q_j|^2
-  float* sig_part;     // [T][tiles][Q]           per-tile sums over tokens of x . q_j
+  float* s_part;       // [T][slices][N][qpad(Q)] per-slice x . q_j (only with several slices)
+  float* g_part;       // [T][slices][N]          per-slice |x|^2 (only with several slices)
+  float* qg_part;      // [T][slices][Q]          per-slice |q_j|^2
+  float* sig_part;     // [T][tiles][slices][Q]   per-unit sums over tokens of x . q_j
   float* pool_part;    // [T][tiles][C]           per-tile channel sums
   float* tok_score;    // [T*N]
   int32_t* rank;       // [T*N]                   selection rank of each token in its frame
@@ -260,13 +341,15 @@ inline size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 // split: room for the filter-bank operator rows when the problem uses them
 // (without it the modulator runs its fused form, which keeps them in LDS).
-inline Workspace workspace_carve(const wz_config& c, size_t tiles, char* base, bool split) {
-  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q;
+inline Workspace workspace_carve(const wz_config& c, size_t tiles, size_t slices, char* base, bool split) {
+  const size_t T = c.T, N = size_t(c.H) * c.W, C = c.C, Q = c.Q, QP = qpad(c.Q), S = slices;
   Workspace w;
   size_t off = 0;
   auto take = [&](size_t bytes) { char* p = base ? base + off : nullptr; off += align256(bytes); return p; };
-  w.qg_part = reinterpret_cast<float*>(take(T * Q * 4));
-  w.sig_part = reinterpret_cast<float*>(take(T * tiles * Q * 4));
+  w.s_part = reinterpret_cast<float*>(take(S > 1 ? T * S * N * QP * 4 : 0));
+  w.g_part = reinterpret_cast<float*>(take(S > 1 ? T * S * N * 4 : 0));
+  w.qg_part = reinterpret_cast<float*>(take(T * S * Q * 4));
+  w.sig_part = reinterpret_cast<float*>(take(T * tiles * S * Q * 4));
   w.pool_part = reinterpret_cast<float*>(take(T * tiles * C * 4));
   w.tok_score = reinterpret_cast<float*>(take(T * N * 4));
   w.rank = reinterpret_cast<int32_t*>(take(T * N * 4));
@@ -283,10 +366,11 @@ inline Workspace workspace_carve(const wz_config& c, size_t tiles, char* base, b
   return w;
 }
 inline size_t workspace_bytes_at(const wz_config& c, int tiles, bool split) {
-  return workspace_carve(c, tiles, nullptr, split).bytes;
+  return workspace_carve(c, tiles, 1, nullptr, split).bytes;
 }
 inline Workspace workspace_layout(const wz_config& c, char* base, bool split = true) {
-  return workspace_carve(c, relevance_plan(c).tiles, base, split);
+  const RelPlan pl = relevance_plan(c);
+  return workspace_carve(c, pl.tiles, pl.slices, base, split);
 }
 
 // Several videos in one launch: video v = blockIdx.y of every kernel works
@@ -317,6 +401,8 @@ __host__ __device__ inline P* advance(P* p, long long bytes) {
 }
 inline Workspace advance(const Workspace& w, long long bytes) {
   Workspace o = w;
+  o.s_part = advance(w.s_part, bytes);
+  o.g_part = advance(w.g_part, bytes);
   o.qg_part = advance(w.qg_part, bytes);
   o.sig_part = advance(w.sig_part, bytes);
   o.pool_part = advance(w.pool_part, bytes);
@@ -335,10 +421,11 @@ inline Workspace advance(const Workspace& w, long long bytes) {
 
 // Kernel launchers (each returns hipGetLastError() of its launches; `vs`
 // batches videos, one by default).
-// Streaming pass of stage 1: per-tile partials into ws, a_{t,n} into tok_score.
+// Streaming pass of stage 1: per-unit partials into ws (and a_{t,n} into
+// tok_score unless there are several channel slices).
 hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void* query, float* tok_score,
                                    const Workspace& ws, hipStream_t s, const Videos& vs = Videos{});
-// Per-frame finish of stage 1: r_t and delta_t;
+// Per-frame finish of stage 1: a_{t,n} (several slices), r_t and delta_t;
 // with `order` also every frame's selection ranks and block gates (into
 // ws.rank, ws.byrank, ws.gate) for launch_assign_gather.
 hipError_t launch_frame(const wz_config& c, const Workspace& ws, float* tok_score, float* frame_rel,

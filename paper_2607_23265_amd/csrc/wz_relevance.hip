@@ -4,17 +4,20 @@
 //     x . q_j  (all j),  |x|^2,  |q_j|^2,
 // and per frame the channel sums p_t = sum_n x_{t,n} (the mean's cosine is the
 // sum's) and sigma_j = sum_n x_{t,n} . q_j = p_t . q_j.  It writes them per
-// work unit (and a_{t,n}, final); the per-frame kernel adds the units' partials
-// in a fixed order and forms r_t and delta_t.
+// work unit (and a_{t,n}, final where a workgroup has every channel); the
+// per-frame kernel adds the units' partials in a fixed order and forms r_t and
+// delta_t.
 //
-// Three decompositions, each with every channel in a workgroup:
+// Four decompositions, the first three with every channel in a workgroup:
 //  * token tiles (fp32 inputs; bf16, Q <= 64 and some of 128 < Q <= 256): a
 //    workgroup owns up to 64 tokens of a frame, its waves split the channels;
 //  * shared token tiles (bf16, 64 < Q <= 128, and 32 < Q <= 64 where a CU would
 //    take turns of the former): the waves share each chunk of
 //    the tile and of the query in LDS and split S;
-//  * wide queries (bf16, Q > 128): the waves split the query's columns, which
-//    they read from L2, and share the tile in LDS.
+//  * wide queries (bf16, Q > 128): the waves split the query's columns, each
+//    staging its own in LDS, and share the tile in LDS;
+//  * channel slices (some of bf16, Q > 256): a workgroup owns up to 256 tokens
+//    and a slice of channels.
 #include <type_traits>
 
 #include "wz_device.h"
@@ -22,15 +25,20 @@
 namespace wz {
 namespace {
 
+constexpr int kKStep = 32;   // channels per MFMA K step (16x16x32)
+constexpr int kQMax = 1024;  // validated bound on query tokens
+
 // Per-unit outputs of the streaming pass (layouts in the workspace carve-up).
 struct StreamArgs {
   const void* X;      // [T][H][W][C]
   const void* query;  // [Q][C]
+  float* s_part;
+  float* g_part;
   float* qg_part;
   float* sig_part;
   float* pool_part;
-  float* tok_score;
-  int T, N, C, Q, tiles;
+  float* tok_score;  // written here unless there are several slices
+  int T, N, C, Q, QP, tiles, slices;
   // several queries in one pass (token-tiled path): `query` holds groups x qg
   // rows (Q = groups * qg); query g's scores, column sums and norms go to the
   // buffers above advanced by g * gws bytes, its channel sums are query 0's
@@ -99,6 +107,267 @@ __device__ __forceinline__ void mfma_units(const u32x4 (&A)[MT], const u32x4 (&B
         for (int i = 0; i < MT; ++i)
           acc[i][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(A[i][e]), __uint_as_float(B[n][e]),
                                                            acc[i][n], 0, 0, 0);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Channel slices (bf16, Q > 256 where wide_takes_slices says)
+// ---------------------------------------------------------------------------
+// A workgroup owns up to 256 tokens of a frame (whole frames up to H*W = 256,
+// so the query is read about once per frame) and a slice of at most 1024
+// channels, so that a few frames with long rows fill the chip; each wave holds
+// two 16-row tiles, loads X straight into the MFMA A layout and runs, per
+// 32-channel step, S += X Q^T (the query slice staged in LDS, 16 NTG columns a
+// pass), G += X X^T (diagonal: |x|^2) and P = X I (identity columns: the
+// step's channel sums).  One wave a step adds the query's Gram matrix (diagonal:
+// |q_j|^2).  With one slice the workgroup finishes its tokens' a_{t,n}; with
+// several it writes the partial x . q_j and |x|^2, which the per-frame kernel
+// adds in slice order.
+// NTG: 16-column query tiles per pass over the slice (queries of more tokens
+// take several passes); R: depth of the X prefetch ring in 32-channel steps.
+template <int NTG, int R>
+__global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_slices(
+    int tile_tokens, int kc, const VideoArgs<StreamArgs> va) {
+  const StreamArgs f = va.v[blockIdx.y];
+  const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
+  const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
+  constexpr int MTW = kTilesPerWave;
+  constexpr int MAXW = kMaxWaves / MTW;
+  constexpr int QB = 8;                          // query units staged per thread per batch
+  __shared__ u32x4 s_q[kSliceSteps][NTG][kWave];  // the group's query slice, MFMA B layout
+  __shared__ float s_poolw[MAXW][kSliceSteps * kKStep];  // per-wave channel sums of the slice
+  __shared__ float s_colw[MAXW][NTG * 16];       // per-wave column sums of S
+  __shared__ float s_qgw[MAXW][NTG * 16];        // per-wave |q_j|^2 partials
+  __shared__ float s_xt[kMaxWaves * 16];         // |x| of the tile's tokens (one slice)
+  __shared__ float s_rq[kQMax];                 // 1/|q_j| (one slice)
+
+  int t, tile, sl;
+  slice_of_block(blockIdx.x, f.tiles, f.slices, t, tile, sl);
+  if (t >= f.T) return;
+  const int N = f.N, C = f.C, Q = f.Q, QP = f.QP, S = f.slices;
+  const int tok0 = tile * tile_tokens;
+  const int TM = min(tile_tokens, N - tok0);
+  const int tid = threadIdx.x, nthreads = blockDim.x;
+  // wave index in a scalar register: branches on it must be scalar branches,
+  // since an MFMA under an exec mask still updates every lane
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = nthreads >> 6;
+  const int row = lane & 15, grp = lane >> 4;
+  const int c_lo = sl * kc, c_hi = min(C, c_lo + kc);
+  const int kper = (c_hi - c_lo + kKStep - 1) / kKStep;  // <= kSliceSteps
+
+  const __amdgpu_buffer_rsrc_t xres = make_rsrc(X + (size_t(t) * N + tok0) * C, uint32_t(TM) * C * 2);
+  const __amdgpu_buffer_rsrc_t qres = make_rsrc(query, uint32_t(Q) * C * 2);
+  int xoff[MTW];  // byte offsets of this lane's token rows (A operands) in the tile
+#pragma unroll
+  for (int i = 0; i < MTW; ++i) {
+    const int r = (wave * MTW + i) * 16 + row;
+    xoff[i] = r < TM ? r * C * 2 : kOOB;
+  }
+
+  // identity operands: slot e of the lane with column `row`, K group `grp`
+  // holds channel 8*grp + e of the step; I_s selects channel 16*s + column
+  bf16x8 I0, I1;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    I0[e] = (__bf16)((8 * grp + e == row) ? 1.0f : 0.0f);
+    I1[e] = (__bf16)((8 * grp + e == 16 + row) ? 1.0f : 0.0f);
+  }
+
+  f32x4 G[MTW];
+  float best[MTW][4];  // rows 16*(wave*MTW+i) + 4*grp + e (one slice only)
+#pragma unroll
+  for (int i = 0; i < MTW; ++i) {
+    G[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) best[i][e] = -INFINITY;
+  }
+  const int groups = (Q + NTG * 16 - 1) / (NTG * 16);
+
+  bf16x8 a[R][MTW];  // X prefetch ring: slot r holds the steps ks = r (mod R)
+  auto issue = [&](int ks, bf16x8 (&dst)[MTW]) {
+    const int c = c_lo + ks * kKStep + grp * 8;
+    const bool ok = ks < kper && c < c_hi;
+#pragma unroll
+    for (int i = 0; i < MTW; ++i) dst[i] = buf_load_bf16x8(xres, ok ? xoff[i] + c * 2 : kOOB);
+  };
+
+  for (int g = 0; g < groups; ++g) {
+    const int qg0 = g * NTG * 16;
+    f32x4 Sacc[MTW][NTG], QG[NTG];
+#pragma unroll
+    for (int n = 0; n < NTG; ++n) {
+      QG[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = 0; i < MTW; ++i) Sacc[i][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    // X ring first, then the query slice of the group into LDS: unit
+    // u -> step u / (64 NTG), tile (u / 64) % NTG, lane u % 64
+#pragma unroll
+    for (int r = 0; r < R; ++r) issue(r, a[r]);
+    const int qunits = kper * NTG * kWave;
+    for (int u0 = 0; u0 < qunits; u0 += QB * nthreads) {
+      u32x4 qv[QB];
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        const int u = u0 + tid + k * nthreads;
+        const int l = u & 63, n = (u >> 6) % NTG, ks = u / (NTG * kWave);
+        const int j = qg0 + n * 16 + (l & 15);
+        const int c = c_lo + ks * kKStep + (l >> 4) * 8;
+        const bool ok = u < qunits && j < Q && c < c_hi;
+        qv[k] = buf_load_u32x4(qres, ok ? (j * C + c) * 2 : kOOB);
+      }
+#pragma unroll
+      for (int k = 0; k < QB; ++k) {
+        const int u = u0 + tid + k * nthreads;
+        if (u < qunits) s_q[u / (NTG * kWave)][(u >> 6) % NTG][u & 63] = qv[k];
+      }
+    }
+    __syncthreads();
+
+    auto compute = [&](int ks, const bf16x8 (&x)[MTW], auto pool) {
+      bf16x8 b[NTG];
+#pragma unroll
+      for (int n = 0; n < NTG; ++n) b[n] = __builtin_bit_cast(bf16x8, s_q[ks][n][lane]);
+#pragma unroll
+      for (int n = 0; n < NTG; ++n)
+#pragma unroll
+        for (int i = 0; i < MTW; ++i)
+          Sacc[i][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], b[n], Sacc[i][n], 0, 0, 0);
+      if (ks % nw == wave) {
+        // query Gram matrix of the step (diagonal: |q_j|^2), spread over the waves
+#pragma unroll
+        for (int n = 0; n < NTG; ++n) QG[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[n], b[n], QG[n], 0, 0, 0);
+      }
+      if constexpr (decltype(pool)::value) {
+        f32x4 P0 = {0.f, 0.f, 0.f, 0.f}, P1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+          G[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], x[i], G[i], 0, 0, 0);
+          P0 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], I0, P0, 0, 0, 0);
+          P1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[i], I1, P1, 0, 0, 0);
+        }
+        float v0 = (P0[0] + P0[1]) + (P0[2] + P0[3]);
+        float v1 = (P1[0] + P1[1]) + (P1[2] + P1[3]);
+        v0 = row_sum4(v0);
+        v1 = row_sum4(v1);
+        // lanes 0-15: channels 32ks+0..15 of the slice, lanes 16-31: 32ks+16..31
+        if (lane < 32) s_poolw[wave][ks * kKStep + lane] = lane < 16 ? v0 : v1;
+      }
+    };
+    // Steps 2s and 2s+1 read the two 64-byte halves of the same 128-byte
+    // line of each row, so they are consumed and re-issued as a pair: the
+    // second request of a line then finds the first one's miss in flight
+    // instead of a line the cache may have evicted meanwhile.
+    static_assert(R % 2 == 0, "the ring advances in pairs of steps");
+    auto run = [&](auto pool) {
+      for (int ks0 = 0; ks0 < kper; ks0 += R) {
+#pragma unroll
+        for (int r = 0; r < R; r += 2) {
+          const int ks = ks0 + r;
+          if (ks < kper) compute(ks, a[r], pool);
+          if (ks + 1 < kper) compute(ks + 1, a[r + 1], pool);
+          issue(ks + R, a[r]);
+          issue(ks + 1 + R, a[r + 1]);
+        }
+      }
+    };
+    if (g == 0) run(std::true_type{});
+    else run(std::false_type{});
+    __syncthreads();
+
+    // ---- group epilogue ----
+    const bool diag = (row >> 2) == grp;  // lane holds element (row, row) of a 16x16 tile
+    if (diag) {
+#pragma unroll
+      for (int n = 0; n < NTG; ++n) s_qgw[wave][n * 16 + row] = QG[n][row & 3];
+    }
+#pragma unroll
+    for (int n = 0; n < NTG; ++n) {
+      float v = 0.f;
+#pragma unroll
+      for (int i = 0; i < MTW; ++i) v += (Sacc[i][n][0] + Sacc[i][n][1]) + (Sacc[i][n][2] + Sacc[i][n][3]);
+      v = row_sum4(v);
+      if (lane < 16) s_colw[wave][n * 16 + lane] = v;
+    }
+    if (g == 0) {
+      const __amdgpu_buffer_rsrc_t gres = make_rsrc(f.g_part + (size_t(t) * S + sl) * N, S > 1 ? uint32_t(N) * 4 : 0u);
+      if (diag) {
+#pragma unroll
+        for (int i = 0; i < MTW; ++i) {
+          const int r = (wave * MTW + i) * 16 + row;
+          const float gg = G[i][row & 3];
+          if (S == 1) s_xt[r] = sqrtf(gg);
+          else buf_store_f32(gg, gres, r < TM ? (tok0 + r) * 4 : kOOB);
+        }
+      }
+      // the slice's channel sums, waves added in order
+      const __amdgpu_buffer_rsrc_t pres =
+          make_rsrc(f.pool_part + (size_t(t) * f.tiles + tile) * C, uint32_t(C) * 4);
+      for (int c = tid; c < kper * kKStep; c += nthreads) {
+        float s = 0.f;
+        for (int w = 0; w < nw; ++w) s += s_poolw[w][c];
+        buf_store_f32(s, pres, c_lo + c < c_hi ? (c_lo + c) * 4 : kOOB);
+      }
+    }
+    __syncthreads();
+    if (tid < NTG * 16) {
+      const int j = qg0 + tid;
+      float qq = 0.f, sg = 0.f;
+      for (int w = 0; w < nw; ++w) {
+        qq += s_qgw[w][tid];
+        sg += s_colw[w][tid];
+      }
+      if (j < Q) {
+        if (S == 1) s_rq[j] = qq > 0.f ? 1.0f / sqrtf(qq) : 0.f;
+        if (tile == 0) f.qg_part[(size_t(t) * S + sl) * Q + j] = qq;
+        f.sig_part[((size_t(t) * f.tiles + tile) * S + sl) * Q + j] = sg;
+      }
+    }
+    __syncthreads();
+    const __amdgpu_buffer_rsrc_t sres =
+        make_rsrc(f.s_part + (size_t(t) * S + sl) * N * QP, S > 1 ? uint32_t(N) * QP * 4 : 0u);
+#pragma unroll
+    for (int n = 0; n < NTG; ++n) {
+      const int j = qg0 + n * 16 + row;  // this lane's column
+      if (S == 1) {
+        const float rq = j < Q ? s_rq[j] : 0.f;
+#pragma unroll
+        for (int i = 0; i < MTW; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) best[i][e] = fmaxf(best[i][e], j < Q ? Sacc[i][n][e] * rq : -INFINITY);
+      } else {
+#pragma unroll
+        for (int i = 0; i < MTW; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = (wave * MTW + i) * 16 + 4 * grp + e;
+            buf_store_f32(Sacc[i][n][e], sres, (r < TM && j < Q) ? ((tok0 + r) * QP + j) * 4 : kOOB);
+          }
+      }
+    }
+  }
+
+  if (S == 1) {
+    // max over the 16 columns held by the lanes of this K group
+#pragma unroll
+    for (int i = 0; i < MTW; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) best[i][e] = fmaxf(best[i][e], __shfl_xor(best[i][e], m, kWave));
+    if (row == 0) {
+#pragma unroll
+      for (int i = 0; i < MTW; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = (wave * MTW + i) * 16 + 4 * grp + e;
+          if (r < TM) {
+            const float xn = s_xt[r];
+            f.tok_score[size_t(t) * N + tok0 + r] = xn > 0.f ? best[i][e] / xn : 0.f;
+          }
+        }
+    }
   }
 }
 
@@ -1140,16 +1409,16 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     for (int e = 0; e < V; ++e) {
       const int q0 = e * G, n = std::min(G, vs.V - q0);
       const Workspace w = advance(ws, q0 * vs.ws);
-      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.qg_part, w.sig_part, w.pool_part,
-                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, pl.tiles, n,
-                           c.Q, vs.ws};
+      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.s_part, w.g_part, w.qg_part, w.sig_part, w.pool_part,
+                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, qpad(c.Q * n), pl.tiles,
+                           pl.slices, n, c.Q, vs.ws};
     }
   } else {
     for (int v = 0; v < vs.V; ++v) {
       const Workspace w = advance(ws, v * vs.ws);
-      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.qg_part, w.sig_part,
-                           w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q,
-                           pl.tiles};
+      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.s_part, w.g_part, w.qg_part, w.sig_part,
+                           w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q, qpad(c.Q),
+                           pl.tiles, pl.slices};
     }
   }
   if (pl.kind == kRelTok) {
@@ -1165,6 +1434,10 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     else if (pl.ntg == 4) hipLaunchKernelGGL((k_relevance_wg<2, 1>), grid, block, 0, s, pl.tile_tokens, va);
     else if (pl.rtw == 1) hipLaunchKernelGGL((k_relevance_wg<1, 2>), grid, block, 0, s, pl.tile_tokens, va);
     else hipLaunchKernelGGL((k_relevance_wg<2, 2>), grid, block, 0, s, pl.tile_tokens, va);
+  } else if (pl.kind == kRelSlices) {
+    if (va.v[0].groups > 1 || pl.mt > kMaxWaves || pl.kc > kSliceSteps * kKStep) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_relevance_slices<2, 4>), dim3(pl.grid, V), dim3((pl.mt + 1) / 2 * kWave), 0, s, pl.tile_tokens,
+                       pl.kc, va);
   } else {
     if (va.v[0].groups > 1 || pl.mt > 4) return hipErrorInvalidValue;
     switch (pl.mt) {

@@ -9,7 +9,7 @@ import libutil
 from paper_2607_23265_amd import wavezip as wz
 from paper_2607_23265_amd.csrc import build
 
-TOK, WG, WIDE = range(3)
+TOK, WG, WIDE, SLICES = range(4)
 SCRATCH = 32 << 20
 CUS = 256
 
@@ -92,6 +92,26 @@ def test_passes_or_one_pass(plan, T, H, W, C, Q, kind):
     assert p["kind"] == kind and (kind == WIDE or p["tile_tokens"] <= 32)
 
 
+# wz_relevance in us, channel slices / one pass; from 128 to 8192 channels the one pass throughout
+@pytest.mark.parametrize("T,H,W,C,Q,kind", [
+    (3, 33, 2, 64408, 816, SLICES),    # 1280 / 3117
+    (1, 5, 12, 61904, 850, SLICES),    # 1242 / 2826
+    (2, 26, 2, 32008, 397, SLICES),    # 318 / 718
+    (8, 10, 12, 32768, 300, SLICES),   # 298 / 439
+    (705, 13, 57, 56, 817, SLICES),    # 653 / 795
+    (8, 14, 14, 16384, 1024, WIDE),    # 847 / 673
+    (64, 7, 7, 16384, 300, WIDE),      # 459 / 236
+    (1, 6, 8, 65536, 300, WIDE),       # frames of fewer than 49 tokens
+    (1, 7, 7, 8192, 300, WIDE), (200, 28, 28, 128, 512, WIDE), (2, 7, 7, 8200, 256, WIDE),
+    # the shapes of test_gpu_slices
+    (2, 7, 7, 8200, 257, SLICES), (1, 7, 8, 16384, 301, SLICES), (3, 9, 9, 10008, 385, SLICES),
+    (9, 5, 10, 20488, 1024, SLICES), (1, 16, 16, 65536, 260, SLICES), (100, 60, 60, 8, 1000, SLICES),
+])
+def test_slices_or_one_pass(plan, T, H, W, C, Q, kind):
+    """More than 256 query tokens: the kernel that measured faster."""
+    assert plan(T, H, W, C, Q)["kind"] == kind
+
+
 def wide_cost(T, tiles, sub, mt):
     """Turns of a CU, times the 16-row tiles and the query reads (as long as four of them) of its stretches."""
     return -(-(-(-T // 8) * 8 * tiles) // CUS) * sub * (mt + 4)
@@ -121,5 +141,5 @@ def test_wide_query_tiles_within_the_scratch(plan, T, H, W, C, Q, tiles):
 
 def test_wide_query_operator_rows_stay_in_the_scratch(plan):
     """A filter-bank call whose operator rows fitted the scratch beside coarser tiles' sums keeps them there."""
-    p = plan(418, 31, 29, 24, 620, basis=wz.WZ_DB4, B=4842)
+    p = plan(325, 35, 24, 280, 473, basis=wz.WZ_DB4, B=6042)
     assert p["kind"] == WIDE and p["bytes"] <= SCRATCH
