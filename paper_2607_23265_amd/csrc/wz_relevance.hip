@@ -1340,7 +1340,16 @@ void launch_tok_waves(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V,
       return;
     }
   }
-  hipLaunchKernelGGL((k_relevance_tok<In, NTG, IPC, false, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), 0, s,
+  // Tiles of 9 to 24 long rows that come from HBM (X beyond the 256 MB Infinity
+  // Cache): LDS enough that one workgroup runs on a CU, not two or three whose
+  // rows are so many more streams (Q <= 16, one / several: T = 270, 23x1, C = 22368
+  // 89.1 / 95.1 us; T = 597, 22x1, C = 51224 455 / 477; T = 1850, 8x1, C = 19064,
+  // shorter tiles, 244 / 221; T = 304, 26x1, C = 8512, 135 MB, 42.1 / 40.5).
+  constexpr size_t kHalf = kTokLdsMax / 2 + 1024;
+  const bool alone = sizeof(In) == 2 && NTG == 1 && (IPC == 2 || IPC == 3) && va.v[0].C > kTokPoolMax &&
+                     size_t(va.v[0].T) * va.v[0].N * va.v[0].C * 2 > (size_t(256) << 20);
+  const size_t lds = alone && tok_lds(NTG, IPC, WV) < kHalf ? kHalf - tok_lds(NTG, IPC, WV) : 0;
+  hipLaunchKernelGGL((k_relevance_tok<In, NTG, IPC, false, MODE, WV>), dim3(pl.grid, V), dim3(WV * kWave), lds, s,
                      pl.tile_tokens, va);
 }
 template <typename In, int NTG, int IPC, int MODE>
