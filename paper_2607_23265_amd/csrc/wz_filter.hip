@@ -42,8 +42,9 @@
 // the first, while the slices of the workgroups on an XCD fit its L2).
 // Split form (bf16 inputs on frames where LDS holds full-frame rows for at
 // most 16 kept tokens, which would read the slice from memory once per
-// chunk): the same kernel with ROWS, one workgroup per frame, does 1-3 and
-// writes the rows to the workspace instead of contracting them; then
+// chunk): the same kernel with ROWS, up to four workgroups per frame that deal
+// the chunks among them, does 1-3 and writes the rows to the workspace instead
+// of contracting them; then
 // k_filter_contract keeps up to 48 rows in its accumulators while each wave
 // streams its 128 channels of the frame once.
 // Supported: H, W <= 64, H*W <= 1024 (the host checks).
@@ -209,9 +210,10 @@ __device__ __forceinline__ void contract_rows(const ContractArgs& a) {
   }
 }
 
-// ROWS (bf16 inputs): the row kernel of the split form, one workgroup per
-// frame: steps 1-3b, then the chunk's operator rows (MFMA form) go to
-// f.rows and their flat indices to out_index, for k_filter_contract.
+// ROWS (bf16 inputs): the row kernel of the split form, up to four workgroups
+// per frame, each every parts-th chunk: steps 1-3b, then the chunk's operator
+// rows (MFMA form) go to f.rows and their flat indices to out_index, for
+// k_filter_contract.
 template <typename In, typename Out, int KR, bool ROWS = false>
 __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<FilterArgs> va, const Bank bank) {
   constexpr int RW = KR / kFWaves;  // rows a wave contracts
@@ -223,7 +225,8 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
   if (t >= f.T) return;  // whole workgroup
   const int H = f.H, W = f.W, N = H * W, F = bank.F, C = f.C;
   const int nh = bank_len(H, F), nw = bank_len(W, F);
-  // with the offsets given, a frame that keeps nothing is done; otherwise
+  const int first = ROWS ? sl * KR : 0;  // the workgroup's first kept token
+  // with the offsets given, a frame that keeps nothing for it is done; otherwise
   // wave 0 computes the budgets (from r and delta, the selection kernel's
   // one-wave arithmetic) while the other waves take the frame's ranks and
   // build the tables
@@ -234,7 +237,7 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
     base = f.offset[t];
     nt = min(max(f.offset[t + 1] - int(base), 0), N);
     total = min((long long)f.offset[f.T], f.B);
-    if (nt == 0) return;  // whole workgroup
+    if (nt <= first) return;  // whole workgroup
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   // threads that rank and build while wave 0 computes the budgets
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
         f.offset_out[i] = s_off[i];
       }
     }
-    if (nt == 0) return;  // whole workgroup
+    if (nt <= first) return;  // whole workgroup
   }
   {
     // the frame's extremes, as the ranking formed them; M by Eq. (7)
@@ -405,7 +408,7 @@ __global__ __launch_bounds__(kFThreads) void k_filter_assign(const VideoArgs<Fil
   const __amdgpu_buffer_rsrc_t xres = make_rsrc(static_cast<const In*>(f.X) + size_t(t) * N * C, uint32_t(N) * rb);
   const int xoff = vok ? v * 8 * int(sizeof(In)) : kOOB;
 
-  for (int c0 = ROWS ? sl * KR : 0; c0 < nt; c0 += ROWS ? S * KR : KR) {
+  for (int c0 = first; c0 < nt; c0 += ROWS ? S * KR : KR) {
     // ---- 3a. B1_i(w') = sum_j (1 - G_ij) E'_j(w'), B2_i(w') = sum_j G_ij P'_j(w')
     // for the chunk's rows, i over the coefficients reaching the row's h ----
     for (int q = tid; q < KR * kMaxAct * W; q += kFThreads) {
