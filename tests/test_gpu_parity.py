@@ -135,8 +135,8 @@ def test_workspace_reuse_across_shapes():
 @pytest.mark.parametrize("T", [1, 2, 3, 63, 64, 65, 100, 128, 129, 200, 255, 256, 257, 1023, 1024, 1025, 2048])
 def test_stage_temporal_budget_random(T):
     """Random fp32 r and delta straight into wz_temporal_budget, up to the 2048-frame limit: one frame per
-    lane of one wave up to 64 frames, four per lane up to 256 (with tau = 0.5 the frame filter drops frames,
-    so the retained positions move), a workgroup above."""
+    lane of one wave up to 64 frames, two, four or eight per lane up to 512 (with tau = 0.5 the frame filter
+    drops frames, so the retained positions move), a workgroup above."""
     rng = np.random.default_rng(T)
     for trial in range(4):
         N = int(rng.choice([1, 3, 196]))

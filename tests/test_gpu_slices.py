@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 # whole frames with several slices: four to sixteen 16-row tiles, the last ragged; a last slice short of a step, or of
-# its steps; queries past a pass of 32 columns, not a multiple of 4 (the partial scores' padding) and the most there are.
+# its steps; queries past a pass of 32 columns, not a multiple of 4 (the partial scores' padding), the most there are.
 # One slice, several tiles a frame: rows of one step and of two.
 SHAPES = [(2, 7, 7, 8200, 257), (1, 7, 8, 16384, 301), (3, 9, 9, 10008, 385), (9, 5, 10, 20488, 1024),
           (1, 16, 16, 65536, 260), (100, 60, 60, 8, 1000), (705, 13, 57, 56, 817)]

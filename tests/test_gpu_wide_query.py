@@ -1,8 +1,8 @@
 """The pass for bf16 queries of more than 128 tokens at the edges of its tiles, passes and stretches.
 
-Tolerance: the inputs are exact in both, the pass sums bf16 products in fp32 (chains of C / 32 MFMA steps and at most 4
-rounded terms in each), so its rounding stays near 1e-7: as for fp32 inputs, 1e-5 relative with a floor of a tenth of
-the largest value.
+Tolerance: the inputs are exact in both, the pass sums bf16 products in fp32 (chains of four 64-channel chunks, eight
+MFMA steps, added up in second accumulators), so its rounding stays near 1e-7: as for fp32 inputs, 1e-5 relative with a
+floor of a tenth of the largest value.
 """
 import numpy as np
 import pytest
@@ -11,6 +11,7 @@ torch = pytest.importorskip("torch")
 
 import gpu_util as G
 import oracle
+import test_gpu_slices as slices
 from libutil import ensure_built
 from paper_2607_23265_amd import synth
 from paper_2607_23265_amd import wavezip as wz
@@ -26,11 +27,12 @@ def _lib():
     ensure_built()
 
 
-# (T, H, W, C, Q): stretches of one to four 16-row tiles, a ragged last tile, one token; channels short of a 64-channel
-# chunk, at and past the ring of four, beyond 8192; queries at the edges of a 16-column tile, of 256 columns and of one,
-# two and three passes
+# (T, H, W, C, Q): stretches of one to four 16-row tiles with two and three column tiles a wave, a ragged last tile, one
+# token; channels short of a 64-channel chunk, at and past the ring of four, beyond 8192; queries at the edges of a
+# 16-column tile, of 256 columns and of one, two and three passes
 SHAPES = [(3, 1, 1, 8, 129), (2, 4, 4, 64, 256), (300, 3, 3, 72, 257), (260, 5, 5, 264, 300), (260, 6, 8, 256, 384),
-          (260, 7, 7, 320, 385), (3, 13, 13, 136, 400), (2, 9, 9, 584, 768), (2, 5, 7, 8200, 140), (9, 8, 8, 96, 1024)]
+          (260, 7, 7, 320, 385), (3, 13, 13, 136, 400), (2, 9, 9, 584, 768), (2, 5, 7, 8200, 140), (9, 8, 8, 96, 1024),
+          (260, 8, 8, 264, 300), (260, 7, 9, 136, 700), (260, 4, 8, 136, 200), (260, 5, 9, 136, 129)]
 
 
 @pytest.mark.parametrize("T,H,W,C,Q", SHAPES)
@@ -78,6 +80,16 @@ def test_stretches_within_the_scratch():
     torch.cuda.synchronize()
     for got, want, what in ((a, torch.cat(a64), "a"), (r, (pn @ qn.t()).amax(1), "r"), (d, d64, "delta")):
         assert G.within(got.cpu().numpy(), want.cpu().numpy(), G.TOL_F32_IN, what)
+
+
+# one tile a frame; two and three, the last one shorter, its last stretch ragged; one pass and two (the channel and
+# column sums of a stretch's passes add to those of the stretches before)
+STRETCHES = [(256, 15, 15, 8192, 400), (128, 19, 21, 9216, 130), (128, 19, 21, 9216, 400), (140, 19, 21, 8000, 400)]
+
+
+@pytest.mark.parametrize("T,H,W,C,Q", STRETCHES)
+def test_stretches(T, H, W, C, Q):
+    slices.test_slices(T, H, W, C, Q)  # a, r and delta against 64 bits
 
 
 @pytest.mark.parametrize("T,H,W,C,Q", [(3, 5, 5, 264, 300), (9, 6, 8, 72, 700), (2, 1, 1, 8, 1024)])

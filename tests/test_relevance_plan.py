@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 import libutil
+import test_gpu_wide_query as wide
 from paper_2607_23265_amd import wavezip as wz
 from paper_2607_23265_amd.csrc import build
 
@@ -137,6 +138,16 @@ def test_wide_query_tiles_within_the_scratch(plan, T, H, W, C, Q, tiles):
     p = plan(T, H, W, C, Q)
     assert p["kind"] == WIDE and p["bytes"] <= SCRATCH
     assert p["tiles"] == tiles and p["sub"] > 1 and p["mt"] <= 4 and p["sub"] * 16 * p["mt"] >= p["tile_tokens"]
+
+
+def test_wide_shapes_reach_every_form(plan):
+    """The shapes of test_gpu_wide_query run every instantiation of the one-pass kernel, and stretches of one and of
+    several tiles a frame with one and two passes over the query."""
+    forms = [p for p in (plan(*s) for s in wide.SHAPES) if p["kind"] == WIDE]
+    assert {(p["mt"], p["ntw"]) for p in forms} == {(m, n) for m in (1, 2, 3, 4) for n in (2, 3)}
+    stretches = [(s, plan(*s)) for s in wide.STRETCHES]
+    assert all(p["kind"] == WIDE and p["sub"] > 1 for _, p in stretches)
+    assert {(p["tiles"] > 1, s[4] > 384) for s, p in stretches} == {(False, True), (True, False), (True, True)}
 
 
 def test_wide_query_operator_rows_stay_in_the_scratch(plan):
