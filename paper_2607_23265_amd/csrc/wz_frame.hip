@@ -17,6 +17,8 @@
 // frame's partial channel sums.  Every partial is added in a fixed order, so
 // results do not depend on timing, and first loads are issued before the first
 // one is used.
+#include <type_traits>
+
 #include "wz_rank.h"
 
 namespace wz {
@@ -27,8 +29,6 @@ constexpr int kThreads = 256;
 constexpr int kWideThreads = 1024;  // scores from slice partials, or frames split into many tiles
 
 struct FrameArgs {
-  const float* s_part;     // [T][S][N][QP]   (several slices)
-  const float* g_part;     // [T][S][N]       (several slices)
   const float* qg_part;    // [T][S][Q]
   const float* sig_part;   // [T][tiles][S][Q]
   const float* pool_part;  // [T][tiles][C]
@@ -39,16 +39,24 @@ struct FrameArgs {
   int32_t* byrank;         // [T][N]
   float* gate;             // [T][N]
   float* gate2;            // [T][N] level-2 gates, or null (one spatial level)
-  int T, N, H, W, C, Q, QP, tiles, slices;
-  int order;               // the order role runs
+  int T, N, H, W, C, Q, tiles;
   int roles;               // workgroups per frame: 1 + (scores or order role)
   float lam;
 };
-static_assert(sizeof(VideoArgs<FrameArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
+// Several channel slices (S > 1).
+struct SliceFrameArgs : FrameArgs {
+  const float* s_part;  // [T][S][N][QP]
+  const float* g_part;  // [T][S][N]
+  int QP, slices;
+  int order;            // the order role runs
+};
+static_assert(sizeof(VideoArgs<SliceFrameArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
+template <bool SL>
+using FrameArgsOf = std::conditional_t<SL, SliceFrameArgs, FrameArgs>;
 
 // scores (SL: several slices) and selection order and gates of frame t
 template <int NTH, bool SL>
-__device__ void order_role(const FrameArgs& f, int t) {
+__device__ void order_role(const FrameArgsOf<SL>& f, int t) {
   constexpr int kNW = NTH / kWave;
   __shared__ float s_mm[2 * kNW];
   __shared__ int s_start[kBins], s_fill[kBins];
@@ -193,7 +201,7 @@ __device__ void order_role(const FrameArgs& f, int t) {
 
 // r_t and delta_t of frame t (SL: several slices)
 template <int NTH, bool SL>
-__device__ void lead_role(const FrameArgs& f, int t) {
+__device__ void lead_role(const FrameArgsOf<SL>& f, int t) {
   constexpr int kNW = NTH / kWave;
   // tiles of the channel sums loaded at once (1024 threads: every tile of a
   // frame split into up to 8, one vector each, so the reads take one round)
@@ -201,7 +209,9 @@ __device__ void lead_role(const FrameArgs& f, int t) {
   __shared__ double s_red[4][kNW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int C = f.C, Q = f.Q, tiles = f.tiles, C4 = C / 4;
-  const int S = SL ? f.slices : 1, K = tiles * S;
+  int S = 1;
+  if constexpr (SL) S = f.slices;
+  const int K = tiles * S;
   const __amdgpu_buffer_rsrc_t pbres = make_rsrc(f.pool_part + size_t(t) * tiles * C, uint32_t(tiles) * C * 4);
   const __amdgpu_buffer_rsrc_t pares =
       make_rsrc(f.pool_part + size_t(t > 0 ? t - 1 : 0) * tiles * C, t > 0 ? uint32_t(tiles) * C * 4 : 0u);
@@ -300,8 +310,8 @@ __device__ void lead_role(const FrameArgs& f, int t) {
 // frame runs on the XCD that streamed it), role (b / 8) % roles; the last role
 // is the lead.
 template <int NTH, bool SL = false>
-__global__ __launch_bounds__(NTH) void k_frame(const VideoArgs<FrameArgs> va) {
-  const FrameArgs& f = va.v[blockIdx.y];
+__global__ __launch_bounds__(NTH) void k_frame(const VideoArgs<FrameArgsOf<SL>> va) {
+  const FrameArgsOf<SL>& f = va.v[blockIdx.y];
   const int b = blockIdx.x, xcd = b % kXcds, slot = b / kXcds;
   const int t = (slot / f.roles) * kXcds + xcd, role = slot % f.roles;
   if (t >= f.T) return;
@@ -321,13 +331,11 @@ hipError_t launch_frame(const wz_config& c, const Workspace& ws, float* tok_scor
   VideoArgs<FrameArgs> va{};
   for (int v = 0; v < vs.V; ++v) {
     const Workspace w = advance(ws, v * vs.ws);
-    va.v[v] = FrameArgs{w.s_part,   w.g_part,  w.qg_part,
-                        w.sig_part, shared ? ws.pool_part : w.pool_part, advance(tok_score, v * vs.ws),
+    va.v[v] = FrameArgs{w.qg_part, w.sig_part, shared ? ws.pool_part : w.pool_part, advance(tok_score, v * vs.ws),
                         advance(frame_rel, v * vs.ws), advance(frame_delta, v * vs.ws), w.rank,
                         w.byrank,   w.gate,    c.spatial_levels == 2 && order ? w.gate2 : nullptr, c.T,
                         N,          c.H,       c.W,
-                        c.C,        c.Q,       qpad(c.Q),
-                        pl.tiles,   pl.slices, order ? 1 : 0,
+                        c.C,        c.Q,       pl.tiles,
                         roles,      c.lambda_};
   }
   // key 8 B; rank, byrank, gate, bin order (and level-2 gate) 4 B
@@ -336,8 +344,14 @@ hipError_t launch_frame(const wz_config& c, const Workspace& ws, float* tok_scor
   // 1024 threads when the scores come from slice partials, or when frames are
   // split into many tiles (few frames: the lead's reads spread over more threads
   // and go out in one round)
-  if (pl.slices > 1) hipLaunchKernelGGL((k_frame<kWideThreads, true>), grid, dim3(kWideThreads), lds, s, va);
-  else if (pl.tiles >= 8) hipLaunchKernelGGL((k_frame<kWideThreads>), grid, dim3(kWideThreads), lds, s, va);
+  if (pl.slices > 1) {
+    VideoArgs<SliceFrameArgs> sa{};
+    for (int v = 0; v < vs.V; ++v) {
+      const Workspace w = advance(ws, v * vs.ws);
+      sa.v[v] = SliceFrameArgs{va.v[v], w.s_part, w.g_part, qpad(c.Q), pl.slices, order ? 1 : 0};
+    }
+    hipLaunchKernelGGL((k_frame<kWideThreads, true>), grid, dim3(kWideThreads), lds, s, sa);
+  } else if (pl.tiles >= 8) hipLaunchKernelGGL((k_frame<kWideThreads>), grid, dim3(kWideThreads), lds, s, va);
   else hipLaunchKernelGGL((k_frame<kThreads>), grid, dim3(kThreads), lds, s, va);
   return hipGetLastError();
 }

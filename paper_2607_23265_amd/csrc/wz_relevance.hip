@@ -32,20 +32,25 @@ constexpr int kQMax = 1024;  // validated bound on query tokens
 struct StreamArgs {
   const void* X;      // [T][H][W][C]
   const void* query;  // [Q][C]
-  float* s_part;
-  float* g_part;
   float* qg_part;
   float* sig_part;
   float* pool_part;
-  float* tok_score;  // written here unless there are several slices
-  int T, N, C, Q, QP, tiles, slices;
+  float* tok_score;
+  int T, N, C, Q, tiles;
   // several queries in one pass (token-tiled path): `query` holds groups x qg
   // rows (Q = groups * qg); query g's scores, column sums and norms go to the
   // buffers above advanced by g * gws bytes, its channel sums are query 0's
   int groups = 1, qg = 0;
   long long gws = 0;
 };
-static_assert(sizeof(VideoArgs<StreamArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
+// Channel slices (arguments that every launch would carry cost it about 0.2 us);
+// with several, tok_score is left to the per-frame kernel.
+struct SliceArgs : StreamArgs {
+  float* s_part;
+  float* g_part;
+  int QP, slices;
+};
+static_assert(sizeof(VideoArgs<SliceArgs>) <= 4096, "per-video arguments exceed the kernel argument limit");
 
 // bf16 dot2 helpers of the token-tiled path
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -127,8 +132,8 @@ __device__ __forceinline__ void mfma_units(const u32x4 (&A)[MT], const u32x4 (&B
 // take several passes); R: depth of the X prefetch ring in 32-channel steps.
 template <int NTG, int R>
 __global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_slices(
-    int tile_tokens, int kc, const VideoArgs<StreamArgs> va) {
-  const StreamArgs f = va.v[blockIdx.y];
+    int tile_tokens, int kc, const VideoArgs<SliceArgs> va) {
+  const SliceArgs f = va.v[blockIdx.y];
   const uint16_t* __restrict__ X = static_cast<const uint16_t*>(f.X);
   const uint16_t* __restrict__ query = static_cast<const uint16_t*>(f.query);
   constexpr int MTW = kTilesPerWave;
@@ -1418,16 +1423,16 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     for (int e = 0; e < V; ++e) {
       const int q0 = e * G, n = std::min(G, vs.V - q0);
       const Workspace w = advance(ws, q0 * vs.ws);
-      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.s_part, w.g_part, w.qg_part, w.sig_part, w.pool_part,
-                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, qpad(c.Q * n), pl.tiles,
-                           pl.slices, n, c.Q, vs.ws};
+      va.v[e] = StreamArgs{X, advance(query, q0 * vs.q), w.qg_part, w.sig_part, w.pool_part,
+                           advance(tok_score, q0 * vs.ws), c.T, c.H * c.W, c.C, c.Q * n, pl.tiles, n,
+                           c.Q, vs.ws};
     }
   } else {
     for (int v = 0; v < vs.V; ++v) {
       const Workspace w = advance(ws, v * vs.ws);
-      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.s_part, w.g_part, w.qg_part, w.sig_part,
-                           w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q, qpad(c.Q),
-                           pl.tiles, pl.slices};
+      va.v[v] = StreamArgs{advance(X, v * vs.x), advance(query, v * vs.q), w.qg_part, w.sig_part,
+                           w.pool_part, advance(tok_score, v * vs.ws), c.T, c.H * c.W, c.C, c.Q,
+                           pl.tiles};
     }
   }
   if (pl.kind == kRelTok) {
@@ -1445,8 +1450,13 @@ hipError_t launch_relevance_stream(const wz_config& c, const void* X, const void
     else hipLaunchKernelGGL((k_relevance_wg<2, 2>), grid, block, 0, s, pl.tile_tokens, va);
   } else if (pl.kind == kRelSlices) {
     if (va.v[0].groups > 1 || pl.mt > kMaxWaves || pl.kc > kSliceSteps * kKStep) return hipErrorInvalidValue;
+    VideoArgs<SliceArgs> sa{};
+    for (int v = 0; v < V; ++v) {
+      const Workspace w = advance(ws, v * vs.ws);
+      sa.v[v] = SliceArgs{va.v[v], w.s_part, w.g_part, qpad(c.Q), pl.slices};
+    }
     hipLaunchKernelGGL((k_relevance_slices<2, 4>), dim3(pl.grid, V), dim3((pl.mt + 1) / 2 * kWave), 0, s, pl.tile_tokens,
-                       pl.kc, va);
+                       pl.kc, sa);
   } else {
     if (va.v[0].groups > 1 || pl.mt > 4) return hipErrorInvalidValue;
     switch (pl.mt) {
