@@ -1081,7 +1081,11 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
 constexpr int kWideWaves = 8;
 constexpr int kWideThreads = kWideWaves * kWave;
 
-template <int MTW, int NTW>
+// LONE: each channel is summed by itself.  Channel sums by dot2 multiply a channel's
+// neighbour by 0, so an infinity makes its neighbour's sum NaN (and r_t = 0,
+// delta_t = 1); frames of fewer than 49 tokens with more than 256 query tokens have
+// always kept it to its own channel (r_t NaN, delta_t = 0).
+template <int MTW, int NTW, bool LONE>
 __global__ __launch_bounds__(kWideThreads, 2) void k_relevance_wide(int tile_tokens, int sub,
                                                                     const VideoArgs<StreamArgs> va) {
   const StreamArgs f = va.v[blockIdx.y];
@@ -1112,13 +1116,6 @@ __global__ __launch_bounds__(kWideThreads, 2) void k_relevance_wide(int tile_tok
   const __amdgpu_buffer_rsrc_t pres = make_rsrc_uniform(f.pool_part + unit * C, uint32_t(C) * 4);
   uint32_t one_lo = kBf16OneLo, one_hi = kBf16OneHi;
   asm volatile("" : "+v"(one_lo), "+v"(one_hi));  // opaque: keeps them out of inline constants
-  // Channel sums by dot2 multiply a channel's neighbour by 0, so an infinity
-  // makes its neighbour's sum NaN (and r_t = 0, delta_t = 1).  Frames of fewer
-  // than 49 tokens with more than 256 query tokens have always summed each
-  // channel alone (r_t NaN, delta_t = 0 there): the neighbour is masked off.
-  // (Such tiles have at most three 16-row tiles.)
-  uint32_t mask_lo = ~0u, mask_hi = ~0u;
-  if (MTW <= 3 && N < 49 && Q > 256) mask_lo = 0x0000FFFFu, mask_hi = 0xFFFF0000u;
   auto row8_sum = [](float v) {  // the 8 lanes of a load-layout row
     v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0xB1, 0xF, 0xF, false));   // lane ^ 1
     v += __uint_as_float(__builtin_amdgcn_update_dpp(0u, __float_as_uint(v), 0x4E, 0xF, 0xF, false));   // lane ^ 2
@@ -1189,8 +1186,8 @@ __global__ __launch_bounds__(kWideThreads, 2) void k_relevance_wide(int tile_tok
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
               xp = dot2(v[e], v[e], xp);
-              cs[2 * e] = dot2(v[e] & mask_lo, one_lo, 0.f);
-              cs[2 * e + 1] = dot2(v[e] & mask_hi, one_hi, 0.f);
+              cs[2 * e] = LONE ? bf16_lo(v[e]) : dot2(v[e], one_lo, 0.f);
+              cs[2 * e + 1] = LONE ? bf16_hi(v[e]) : dot2(v[e], one_hi, 0.f);
             }
             // lane 8 k + lu ends with channel 8 lu + k's sum over the wave's rows
             const float cw = lane_transpose_sum(cs);
@@ -1320,11 +1317,17 @@ __global__ __launch_bounds__(kWideThreads, 2) void k_relevance_wide(int tile_tok
   }
 }
 
+template <int MTW, bool LONE>
+void launch_wide_cols(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
+  const dim3 grid(pl.grid, V), block(kWideThreads);
+  if (pl.ntw == 2) hipLaunchKernelGGL((k_relevance_wide<MTW, 2, LONE>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
+  else hipLaunchKernelGGL((k_relevance_wide<MTW, 3, LONE>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
+}
 template <int MTW>
 void launch_wide_rows(const RelPlan& pl, const VideoArgs<StreamArgs>& va, int V, hipStream_t s) {
-  const dim3 grid(pl.grid, V), block(kWideThreads);
-  if (pl.ntw == 2) hipLaunchKernelGGL((k_relevance_wide<MTW, 2>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
-  else hipLaunchKernelGGL((k_relevance_wide<MTW, 3>), grid, block, 0, s, pl.tile_tokens, pl.sub, va);
+  if constexpr (MTW <= 3)  // fewer than 49 tokens
+    if (va.v[0].N < 49 && va.v[0].Q > 256) return launch_wide_cols<MTW, true>(pl, va, V, s);
+  launch_wide_cols<MTW, false>(pl, va, V, s);
 }
 
 // LDS of a token-tiled workgroup without the gathered channel sums.
