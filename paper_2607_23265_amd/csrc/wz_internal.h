@@ -26,11 +26,6 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float f) {
 }
 
 // Butterfly sum across the 64 lanes of a wave (every lane gets the total).
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
-  return v;
-}
 __device__ __forceinline__ double wave_sum_f64(double v) {
 #pragma unroll
   for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, kWave);
@@ -308,10 +303,10 @@ __device__ __forceinline__ void slice_of_block(int b, int tiles, int slices, int
 }
 
 constexpr int kMaxFrames = 2048;
-// frames up to which the budget is folded into the selection kernel (one
-// wave computes it: up to 64 frames in registers, up to 256 four frames per
-// lane in LDS); above, one workgroup of its own computes it once, which costs
-// less than every selection workgroup repeating a workgroup-wide budget
+// frames up to which the budget is folded into the selection kernel (one wave
+// computes it in registers, one, two or four frames per lane); above, a launch of
+// its own computes it once (one wave up to 512 frames, eight per lane; 1024
+// threads beyond), instead of every selection workgroup repeating it
 constexpr int kFusedTMax = 256;
 
 // Workspace carve-up (all offsets 256-byte aligned).

@@ -381,7 +381,9 @@ __global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_sl
 // ---------------------------------------------------------------------------
 // (Described for bf16 inputs; an fp32 chunk is 32 channels, the same bytes,
 // and its S runs on v_mfma_f32_16x16x4_f32.  Bound for fp32: HBM up to about
-// 48 query tokens, above that the fp32 MFMA rate, a sixteenth of bf16's.  It
+// 48 query tokens, above that the fp32 MFMA rate, a sixteenth of bf16's (T =
+// 64, 14x14, C = 3584, Q = 32: 49 us for 184 MB of HBM traffic, MFMA busy 47 %
+// of the cycles, vector ALU 25 %, LDS 14 %).  It
 // replaced one wave per token on the vector ALU, which read the whole query
 // from L2 for every token: T = 64, 14x14, C = 3584, Q = 32: 824 -> 51 us; T =
 // 8, 24x24, C = 2504, Q = 96: 1219 -> 56 us.)
@@ -399,7 +401,8 @@ __global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_sl
 //      chunk's channel sums with bf16 dot2 instructions; the channel sums are
 //      reduced across the wave by DPP and lane swaps and gathered in LDS;
 //   3. runs two 32-channel steps of S += X Q^T (v_mfma_f32_16x16x32_bf16) on
-//      four 16-row tiles, reading both operands from its buffers;
+//      the tile's one to four 16-row tiles, reading both operands from its
+//      buffers;
 //   4. re-issues the ring slot for the chunk after next.
 // In the epilogue each wave first reduces its own accumulator rows to
 // sigma_j (lane swaps); then the waves' partial S, |x|^2, |q_j|^2 and sigma_j
@@ -768,17 +771,20 @@ __global__ __launch_bounds__(WV * 64) void k_relevance_tok(int tile_tokens, cons
 // With a wide query, per-wave channel stripes (above) would stage the query
 // once per wave and add every wave's partial S through LDS.  Here the eight
 // waves of a workgroup share each 64-channel chunk: the tile's rows (up to
-// 64 * RTW tokens) and the query's 128 rows are loaded once per workgroup
+// 64 * RTW tokens) and the query's 64 NTW rows are loaded once per workgroup
 // (one 16-byte unit per thread and row group, whole cache lines), staged in a
 // double-buffered LDS stage (16-byte units XOR-swizzled by row), and the
 // waves tile S as 2 row groups x 4 column groups: wave (wr, wc) contracts
 // 16-row tiles wr * 2 RTW .. wr * 2 RTW + 2 RTW - 1 against 16-column tiles
-// 2 wc, 2 wc + 1.  |x|^2, |q_j|^2 and the chunk's channel sums come from the
-// load registers (bf16 dot2), the channel sums added over the waves in wave
-// order through LDS.  One LDS-only barrier per chunk; D chunks of loads in
+// NTW wc .. NTW wc + NTW - 1.  |x|^2, |q_j|^2 and the chunk's channel sums come
+// from the load registers (bf16 dot2), the channel sums added over the waves in
+// wave order through LDS.  One LDS-only barrier per chunk; D chunks of loads in
 // flight in registers.  The row maxima and column sums of S are combined
 // across the waves through LDS at the end, in a fixed order.  Two
-// workgroups share a CU.
+// workgroups share a CU.  Bound: the barrier a chunk and the vector ALU's norms
+// and channel sums (counters at T = 256, 27x27, C = 1152, Q = 128, 111.5 us: vector
+// ALU 45 % of the cycles, LDS 31 %, MFMA 23 %, 446 MB of HBM traffic; T = 96, Q =
+// 48, 48.4 us: 56 %, 27 %, 9 %, 168 MB).
 constexpr int kWgWaves = 8;
 
 template <int RTW, int NTW>
@@ -1066,13 +1072,20 @@ __global__ __launch_bounds__(kWgWaves * 64, 2) void k_relevance_wg(int tile_toke
 // accumulator (one chain of C / 32 steps was three times as far from the 64-bit
 // result).
 // A workgroup owns at most `sub` stretches of 16 MTW tokens of one frame, one
-// after another, with all channels, so a_{t,n} is final here; with sub > 1 (when
-// the partial sums of finer tiles would not fit the scratch) the channel and
-// column sums add up over the stretches in order.  Queries of more than 384
-// tokens take passes over a stretch, channel sums in the first.
-// Bound: LDS, which every wave reads the tile from.  It replaced channel slices
-// with partial scores through memory, dot products on the vector ALU for small
-// frames (Q > 256), and passes of 32 columns over the tile (Q <= 256).
+// after another, with all channels, so a_{t,n} is final here; with sub > 1 (where
+// the partial sums of finer tiles would not fit the scratch and it costs little)
+// the channel and column sums add up over the stretches in order.  Queries of
+// more than 384 tokens take passes over a stretch, channel sums in the first.
+// Bound: staging, the barrier and the contraction follow one another with one
+// workgroup, two waves a SIMD, to a CU; no unit is busy alone (counters at T = 64,
+// 14x14, C = 3584, Q = 300, 69.7 us: vector ALU 36 % of the cycles, LDS 31 % with
+// hardly a bank conflict, MFMA 21 %; a third of the waves' cycles wait for loads
+// or the barrier, a third to issue).  <4, 3> takes all 256 registers and spills
+// eight values that are set before the loops and read between them, none in the
+// loop over chunks, whose loads are counted.  It replaced channel slices with
+// partial scores through memory, dot products on the vector ALU for small frames
+// (Q > 256), and passes of 32 columns over the tile (Q <= 256), but where
+// wide_takes_slices and wide_takes_passes say.
 // wz_relevance at T = 64, 14x14, C = 3584: Q = 130 84 -> 54 us, Q = 300 209 ->
 // 75 us (error against 64 bits 1.3e-7 -> 0.95e-7), Q = 1024 603 -> 221 us; T =
 // 40, 5x5, C = 1024, Q = 300: 1409 -> 23 us.  Four further waves that load X and

@@ -56,8 +56,8 @@ hipError_t launch_budget(const wz_config& c, const float* frame_rel, const float
   if (c.T <= 64) launch_k<kWave, 64>(c, va, vs.V, s);
   else if (c.T <= 128 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 128>(c, va, vs.V, s);
   else if (c.T <= 256 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 256>(c, va, vs.V, s);
-  // (one wave's lane swaps against a workgroup's barriers at every reduction:
-  // a T = 512, 8x8, C = 3584 call 98.9 -> 81.6 us, T = 300 81.6 -> 66.9 us)
+  // (one wave's lane swaps against a workgroup's barriers at every reduction: a T
+  // = 512, 8x8, C = 3584 call 112.6 -> 94.7 us, this kernel 26.8 -> 10.7)
   else if (c.T <= 512 && c.temporal_basis == WZ_HAAR) launch_k<kWave, 512>(c, va, vs.V, s);
   else if (c.T <= 256) launch_k<256, 256>(c, va, vs.V, s);
   else launch_k<1024, kTMax>(c, va, vs.V, s);
