@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kMaxWaves / kTilesPerWave * 64) void k_relevance_sl
 // (Described for bf16 inputs; an fp32 chunk is 32 channels, the same bytes,
 // and its S runs on v_mfma_f32_16x16x4_f32.  Bound for fp32: HBM up to about
 // 48 query tokens, above that the fp32 MFMA rate, a sixteenth of bf16's (T =
-// 64, 14x14, C = 3584, Q = 32: 49 us for 184 MB of HBM traffic, MFMA busy 47 %
+// 64, 14x14, C = 3584, Q = 32: 49 us for 187 MB of HBM traffic, MFMA busy 47 %
 // of the cycles, vector ALU 25 %, LDS 14 %).  It
 // replaced one wave per token on the vector ALU, which read the whole query
 // from L2 for every token: T = 64, 14x14, C = 3584, Q = 32: 824 -> 51 us; T =

@@ -33,7 +33,8 @@ def _lib():
 SHAPES = [(3, 1, 1, 8, 129), (2, 4, 4, 64, 256), (300, 3, 3, 72, 257), (260, 5, 5, 264, 300), (260, 6, 8, 256, 384),
           (260, 7, 7, 320, 385), (3, 13, 13, 136, 400), (2, 9, 9, 584, 768), (2, 5, 7, 8200, 140), (9, 8, 8, 96, 1024),
           (260, 8, 8, 264, 300), (260, 7, 9, 136, 700), (260, 4, 8, 136, 200), (260, 5, 9, 136, 129),
-          (128, 8, 8, 72, 300), (128, 8, 12, 72, 300), (3, 4, 4, 136, 450), (260, 5, 6, 136, 512), (260, 6, 8, 136, 400)]
+          (128, 8, 8, 72, 300), (128, 8, 12, 72, 300), (3, 4, 4, 136, 450), (260, 5, 6, 136, 512),
+          (260, 6, 8, 136, 400)]
 
 
 @pytest.mark.parametrize("T,H,W,C,Q", SHAPES)
