@@ -98,10 +98,11 @@ inline long wide_cost(const wz_config& c, int tiles) {
 }
 // the cheapest count of tiles of at most 64 tokens, the smaller on a tie
 inline int wide_best_tiles(const wz_config& c) {
-  const int N = c.H * c.W;
-  int tiles = (N + 63) / 64;
-  for (int k = tiles + 1; k <= (N + 15) / 16; ++k)
-    if (wide_cost(c, k) < wide_cost(c, tiles)) tiles = k;
+  const int N = c.H * c.W, lo = (N + 63) / 64;
+  int tiles = lo;
+  long best = wide_cost(c, lo);
+  for (int k = lo + 1; k <= (N + 15) / 16; ++k)
+    if (const long cost = wide_cost(c, k); cost < best) best = cost, tiles = k;
   return tiles;
 }
 inline int wide_tiles(const wz_config& c) {
@@ -117,11 +118,13 @@ inline int wide_tiles(const wz_config& c) {
   // 128 tokens 1346); half more above, where the scratch has always held tiles
   // of 256 tokens up to C = 1024 (at most 1.43 times the cost there).
   const long pct = c.Q <= 256 ? 125 : 150;
+  const long most = wide_cost(c, tiles) * pct;
   for (const bool split : {true, false}) {
     if (workspace_bytes_at(c, tiles, split) <= kScratchBytes) break;
     int fit = 0;
+    long best = most / 100 + 1;
     for (int k = (N + 255) / 256; k <= (N + 15) / 16 && workspace_bytes_at(c, k, split) <= kScratchBytes; ++k)
-      if (100 * wide_cost(c, k) <= pct * wide_cost(c, tiles) && (!fit || wide_cost(c, k) < wide_cost(c, fit))) fit = k;
+      if (const long cost = wide_cost(c, k); 100 * cost <= most && cost < best) best = cost, fit = k;
     if (fit) return fit;
   }
   return tiles;
